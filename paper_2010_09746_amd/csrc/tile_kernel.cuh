@@ -587,6 +587,33 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
         return o;
     }
 
+    // Read one word of every 64-byte line of the pass's operation table through
+    // the scalar cache while the tile's own loads are in flight.  The records
+    // are read one at a time, and the first wavefront of a compute unit to
+    // reach one otherwise waits for a miss to memory at each of them (the caches start
+    // a launch without them): with one or two workgroups per compute unit
+    // nothing hides that.  The wavefronts of the workgroup split the lines,
+    // 16 in flight each.  21 qubits, complex64, 30 layers: 39 -> 32 us per
+    // pass (512 workgroups); 26 qubits and above unchanged.  (Vector loads
+    // instead, which stop at the second-level cache: 33 us.)
+    static __device__ __forceinline__ void touch_records(OpPtr ops, int n_ops, uint32_t tid)
+    {
+        using WP = const __attribute__((address_space(4))) uint32_t *;
+        const uint32_t lines = ((uint32_t)n_ops * (uint32_t)sizeof(TileOp)) >> 6;  // whole lines: reads stay inside
+        const WP p = (WP)ops;
+        constexpr uint32_t U = 16, NW = NT / 64;
+        const uint32_t wave = NW > 1 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6)) : 0u;
+        for (uint32_t i = wave * U; i < lines; i += NW * U) {
+            uint32_t x[U];
+#pragma unroll
+            for (uint32_t q = 0; q < U; ++q)
+                x[q] = p[(i + q < lines ? i + q : lines - 1) * 16];
+#pragma unroll
+            for (uint32_t q = 0; q < U; ++q)
+                __asm__ __volatile__("" ::"s"(x[q]));  // keeps the loads
+        }
+    }
+
     // Per-tile read-out of the final amplitudes: sum |a|^2 and sum |a|^2 (1 - 2 b)
     // where b is the bit at physical position zpos (the first qubit), reduced
     // over the workgroup in a fixed order and written to out[0..1].
@@ -654,8 +681,10 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
             });
         };
         if constexpr (PF) {
-            if (t_first < t_end)
+            if (t_first < t_end) {
                 load(v, t_first);
+                touch_records(ops, n_ops, tid);
+            }
             // wait for the first tile here, so that the loop's own waits are only
             // those for the prefetched tile (vmcnt(0): expcnt and lgkmcnt left at
             // their maxima)
@@ -667,6 +696,8 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
             const bool more = PF && t + t_step < t_end;
             if constexpr (!PF) {
                 load(v, t);
+                if (t == t_first)
+                    touch_records(ops, n_ops, tid);
                 __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), as above
             } else if (more)
                 load(w, t + t_step);
