@@ -212,17 +212,20 @@ uint64_t phys_index(uint64_t i, const std::vector<int> &sigma)
 }
 
 // Apply the position map pi (amplitude at x moves to the index whose bit
-// pi[p] is bit p of x) as at most two in-place involutions: along each cycle
-// c_0 -> c_1 -> ... -> c_{L-1} of pi, first c_i -> c_{-i}, then c_i -> c_{1-i}
-// (indices mod L); the composition sends c_i to c_{i+1}.
-// Physical position p of the state moves to pi[p] (PermuteQubits, Section 2).
+// pi[p] is bit p of x): physical position p of the state moves to pi[p]
+// (PermuteQubits, Section 2), in place.
 //
-// The position map's cycles are grouped so that each group's positions, plus
-// the lowest positions (so that every load and store moves 128-byte runs), fit
-// a tile.  A group is one tile pass without gates that writes each tile back
-// with its bits permuted: the tile is closed under the map, so the move stays
-// inside the tile, in place, and every amplitude is read and written once.
-// Cycles too long for a tile go through two in-place involutions instead.
+// Two ways, and the one with fewer launches is taken (every launch reads and
+// writes the amplitudes it moves once, at much the same bandwidth):
+//  * the cycles of pi, grouped so that each group's positions, plus the lowest
+//    positions (so that every load and store moves 128-byte runs), fit a tile.
+//    A group is one tile pass without gates that writes each tile back with its
+//    bits permuted: the tile is closed under the map, so the move stays inside
+//    the tile.  Ties go here (one exchanged pair up to several short cycles);
+//  * at most two involutions: along each cycle c_0 -> c_1 -> ... -> c_{L-1} of
+//    pi, first c_i -> c_{-i}, then c_i -> c_{1-i} (indices mod L); the
+//    composition sends c_i to c_{i+1}.  Only one is left when every cycle is
+//    an exchange.
 void apply_position_map(qs_state *s, const std::vector<int> &pi)
 {
     const int n = s->n;
@@ -233,7 +236,6 @@ void apply_position_map(qs_state *s, const std::vector<int> &pi)
     const int max_k = std::min(n, esize == 16 ? 12 : 13);  // tiles of at most 64 KiB
     std::vector<std::vector<int>> cycles;
     std::vector<char> seen(n, 0);
-    size_t longest = 0;
     for (int p = 0; p < n; ++p) {
         if (seen[p])
             continue;
@@ -242,10 +244,8 @@ void apply_position_map(qs_state *s, const std::vector<int> &pi)
             seen[x] = 1;
             cyc.push_back(x);
         }
-        if (cyc.size() > 1) {
-            longest = std::max(longest, cyc.size());
+        if (cyc.size() > 1)
             cycles.push_back(cyc);
-        }
     }
     if (cycles.empty())
         return;
@@ -261,8 +261,14 @@ void apply_position_map(qs_state *s, const std::vector<int> &pi)
             }
         return k;
     };
-    if (n >= MIN_TILE_BITS && (int)longest + low <= max_k) {
-        std::vector<std::vector<int>> groups;
+    bool fits = n >= MIN_TILE_BITS;
+    int n_inv = 1;
+    for (const auto &c : cycles) {
+        fits = fits && tile_bits(c) <= max_k;
+        n_inv = c.size() > 2 ? 2 : n_inv;
+    }
+    std::vector<std::vector<int>> groups;
+    if (fits) {
         for (const auto &c : cycles) {
             bool placed = false;
             for (auto &g : groups) {
@@ -277,6 +283,8 @@ void apply_position_map(qs_state *s, const std::vector<int> &pi)
             if (!placed)
                 groups.push_back(c);
         }
+    }
+    if (fits && (int)groups.size() <= n_inv) {
         for (const auto &g : groups) {
             std::vector<char> in(n, 0);
             for (int p : g)
