@@ -80,7 +80,7 @@ void plan_batch(int count, const int *n, const qs_gate *const *gates, const int6
                 ro.max_fuse = o.max_fuse;
                 ro.reg_bits = bp.k[c] - QUEUE_LOG_NT;
                 try {
-                    compile_program(gates[c], n_gates[c], n[c], dt, nullptr, ro, bp.progs[c]);
+                    compile_program(gates[c], n_gates[c], n[c], dt, nullptr, ro, bp.progs[c], {}, nullptr, false);
                 } catch (const Error &e) {
                     errs[c] = e.msg;
                 }

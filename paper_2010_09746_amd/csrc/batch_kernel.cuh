@@ -137,10 +137,10 @@ __global__ __launch_bounds__(256) void k_batch_queue(QueueArgs q)
         const auto &P = passes[pi];
         double *part = P.last ? q.partials + 2 * (P.part + t0) : nullptr;
         switch (sh) {
-        case 1: QK::template TK<1>::template run_range<false, true>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
-        case 2: QK::template TK<2>::template run_range<false, true>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
-        case 3: QK::template TK<3>::template run_range<false, true>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
-        default: QK::template TK<4>::template run_range<false, true>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
+        case 1: QK::template TK<1>::template run_range<false, true, false, false>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
+        case 2: QK::template TK<2>::template run_range<false, true, false, false>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
+        case 3: QK::template TK<3>::template run_range<false, true, false, false>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
+        default: QK::template TK<4>::template run_range<false, true, false, false>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
         }
         // every wavefront's stores (and read-out partials) have completed
         __builtin_amdgcn_s_waitcnt(0x0F70);

@@ -1053,6 +1053,117 @@ int schedule_segment(const std::vector<LGate> &lg, const qs_gate *g, const std::
     return remaps;
 }
 
+// Controlled phases that follow each other and share a bit become one OP_FAN.
+//
+// A controlled phase multiplies by d where two bits are 1 and is symmetric in
+// them, and phases commute, so a run of OP_DIAG records with one control and d0
+// = 1 exactly that share one bit (the hub) is the product over the other bits
+// (the spokes) on the amplitudes whose hub bit is 1.  From three phases on the
+// fan is the shorter work: its records cost one multiplication of the hub's
+// amplitudes plus one small factor per lane and spoke, where each OP_DIAG
+// multiplies half or more of the amplitudes it selects from.  A phase on a
+// register slot above 3 cannot be a spoke (the record holds four) and ends a run.
+struct DiagBits {
+    bool ok = false;
+    int bit[2] = {0, 0};  // control, target: slot s as s, thread tile bit b as 16 + b, position p as 64 + p
+};
+
+DiagBits diag_bits(const TileOp &o)
+{
+    DiagBits d;
+    if (o.kind != OP_DIAG || o.m[0] != 1.0 || o.m[1] != 0.0)
+        return d;
+    if (__builtin_popcount(o.rmask) + __builtin_popcount(o.lmask) + __builtin_popcountll(o.hmask) != 1)
+        return d;
+    d.bit[0] = o.rmask ? __builtin_ctz(o.rmask) : o.lmask ? 16 + __builtin_ctz(o.lmask) : 64 + __builtin_ctzll(o.hmask);
+    d.bit[1] = o.slot >= 0 ? o.slot : o.slot == -1 ? 16 + __builtin_ctz(o.tlane) : 64 + __builtin_ctzll(o.hbit);
+    d.ok = d.bit[0] != d.bit[1];
+    return d;
+}
+
+void fuse_phase_fans(std::vector<TileOp> &ops, size_t begin)
+{
+    constexpr size_t MIN_PHASES = 3;
+    // end of the run of phases from i on that share bit `hub`
+    auto run_end = [&](size_t i, int hub) {
+        uint32_t slots = 0;
+        for (; i < ops.size(); ++i) {
+            const DiagBits d = diag_bits(ops[i]);
+            if (!d.ok || (d.bit[0] != hub && d.bit[1] != hub))
+                break;
+            const int sp = d.bit[0] == hub ? d.bit[1] : d.bit[0];
+            if (sp < 16 && (sp > 3 || ((slots >> sp) & 1u)))
+                break;
+            slots |= sp < 16 ? 1u << sp : 0u;
+        }
+        return i;
+    };
+    size_t w = begin;
+    for (size_t i = begin; i < ops.size();) {
+        const DiagBits d = diag_bits(ops[i]);
+        size_t end = i;
+        int hub = 0;
+        for (int t = 0; d.ok && t < 2; ++t) {
+            const size_t e = run_end(i, d.bit[t]);
+            if (e > end) {
+                end = e;
+                hub = d.bit[t];
+            }
+        }
+        if (end < i + MIN_PHASES) {
+            ops[w++] = ops[i++];
+            continue;
+        }
+        TileOp h{};
+        h.kind = OP_FAN;
+        h.slot = hub < 16 ? hub : hub < 64 ? -1 : -2;
+        h.tlane = hub >= 16 && hub < 64 ? 1u << (hub - 16) : 0u;
+        h.hbit = hub >= 64 ? 1ull << (hub - 64) : 0ull;
+        std::vector<TileOp> more;
+        int fill = 4;
+        for (size_t j = i; j < end; ++j) {
+            const TileOp &o = ops[j];
+            const DiagBits b = diag_bits(o);
+            const int sp = b.bit[0] == hub ? b.bit[1] : b.bit[0];
+            const bool outside = o.hmask != 0;
+            if (sp < 16) {
+                h.rmask |= 1u << sp;
+                h.m[2 * sp] = o.m[2];
+                h.m[2 * sp + 1] = o.m[3];
+                h.aux |= outside ? 1u << (FAN_HCTRL + sp) : 0u;
+                continue;
+            }
+            if (fill == 4) {
+                TileOp s{};
+                s.kind = OP_SPOKES;
+                s.hmask = 1ull << 63;
+                s.rmask = ~0u;
+                more.push_back(s);
+                fill = 0;
+            }
+            TileOp &s = more.back();
+            const uint32_t code = sp >= 64 ? SPOKE_OUT | (uint32_t)(sp - 64) : (uint32_t)(sp - 16);
+            s.rmask = (s.rmask & ~(255u << (8 * fill))) | (code << (8 * fill));
+            s.m[2 * fill] = o.m[2];
+            s.m[2 * fill + 1] = o.m[3];
+            s.aux |= outside ? 1u << (FAN_HCTRL + fill) : 0u;
+            ++fill;
+        }
+        // never more records than the phases they replace, so w stays behind i
+        if (1 + more.size() > end - i || more.size() > 255) {
+            while (i < end)
+                ops[w++] = ops[i++];
+            continue;
+        }
+        h.aux |= (uint32_t)more.size();
+        i = end;
+        ops[w++] = h;
+        for (const TileOp &s : more)
+            ops[w++] = s;
+    }
+    ops.resize(w);
+}
+
 // Wavefront-local re-layouts.  The thread-id bits above the lane bits (6 and
 // up) number the wavefronts of a workgroup.  A re-layout that leaves the same
 // tile bits on them moves amplitudes only between the lanes and registers of
@@ -1289,6 +1400,11 @@ void set_direct_io(Launch &L, const std::vector<TileOp> &ops, qs_dtype dt)
             reg[s] = (uint8_t)L.pos[L.log_nt + s];
     };
     L.io = contiguous ? 8u : 0u;
+    for (int i = 0; i < L.op_count; ++i) {
+        const int kind = ops[L.op_begin + i].kind;
+        if (kind == OP_LANE || kind == OP_FAN)
+            L.io |= IO_EXT;
+    }
     plain(L.ld_lane, L.ld_reg);
     plain(L.st_lane, L.st_reg);
     const TileOp *o = ops.data() + L.op_begin;
@@ -1349,7 +1465,7 @@ void tile_args_identity(int k, int log_nt, int log_r, TileArgs &a)
 
 void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int *sigma0_in,
                      const qs_run_opts &o, Program &p, const std::function<void(Program &)> &progress,
-                     const qs_pass_costs *costs)
+                     const qs_pass_costs *costs, bool fans)
 {
     auto t0 = std::chrono::steady_clock::now();
     if (n < 1 || n > MAX_COMPILE_QUBITS)
@@ -1519,6 +1635,8 @@ void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int
                     L.pos = pos;
                     L.op_begin = (int)p.ops.size();
                     p.stats.n_remaps += schedule_segment(lg, g, gi, k, log_r, p.ops, pf, lane_bits, lane_eager);
+                    if (fans)
+                        fuse_phase_fans(p.ops, (size_t)L.op_begin);
                     // lane gates name thread bits of the ascending map
                     if (lane_bits == 0)
                         assign_wave_bits(p.ops, (size_t)L.op_begin, k, log_r, log_nt, direct_low_bits(dt),

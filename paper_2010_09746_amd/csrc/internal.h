@@ -179,9 +179,11 @@ struct Program {
 // Compile a circuit.  With progress, the pass form calls it after each pass
 // iteration, once the launches of every completed segment are in p.launches
 // (and their operations in p.ops); launches already there never change.
+// Without fans, controlled phases stay one operation each (for the batching
+// form's kernel, which has no code for OP_FAN).
 void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int *sigma0,
                      const qs_run_opts &o, Program &p, const std::function<void(Program &)> &progress = {},
-                     const qs_pass_costs *costs = nullptr);
+                     const qs_pass_costs *costs = nullptr, bool fans = true);
 
 }  // namespace qsim
 

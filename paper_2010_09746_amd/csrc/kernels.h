@@ -26,6 +26,10 @@ void launch_tile_f64(const TileArgs &a, uint64_t n_tiles, int log_r, int log_nt,
 // the passes that do not move whole 128-byte lines (plain loads and stores)
 void launch_tile_f32_plain(const TileArgs &a, uint64_t n_tiles, int log_r, int log_nt, hipStream_t st);
 void launch_tile_f64_plain(const TileArgs &a, uint64_t n_tiles, int log_r, int log_nt, hipStream_t st);
+// the passes over whole lines that hold lane gates or phase fans (TileArgs::io
+// bit 5)
+void launch_tile_f32_ext(const TileArgs &a, uint64_t n_tiles, int log_r, int log_nt, hipStream_t st);
+void launch_tile_f64_ext(const TileArgs &a, uint64_t n_tiles, int log_r, int log_nt, hipStream_t st);
 // The same, each tile also writing its per-bit probability sums to zparts
 // (1 + log_r + log_nt doubles per tile, see run_range's ZB read-out); passes
 // over whole 128-byte lines only (TileArgs::io bit 3).

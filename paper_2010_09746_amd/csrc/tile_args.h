@@ -33,10 +33,25 @@ enum TileOpKind : int32_t {
                    // word of m is the slot's new LDS slot (lds_swizzle of lmask)
     OP_LANE = 9,   // dense 2x2 (m[0..7]) on thread-id bit tlane (< 4) of the layout, through
                    // lane exchanges (DPP) instead of a re-layout; no controls
+    OP_FAN = 10,   // controlled phases that share one bit (the hub): where the hub bit is 1,
+                   // multiply by the product of d over the other bits (the spokes) that are 1.
+                   // The hub as OP_DIAG's target (slot, tlane, hbit); rmask: register slots
+                   // 0..3 that are spokes, slot q with d = (m[2q], m[2q+1]); aux & 255: the
+                   // OP_SPOKES records that follow
+    OP_SPOKES = 11 // up to 4 more spokes of the OP_FAN before: byte i of rmask names the bit of
+                   // spoke i (SPOKE_OUT | physical position, else a tile bit on the threads,
+                   // SPOKE_NONE: no spoke), d = (m[2i], m[2i+1]); read by the OP_FAN and skipped
+                   // by the loop (hmask has a bit that no index has)
 };
+
+constexpr uint32_t SPOKE_OUT = 0x80u, SPOKE_NONE = 0xffu;
+// bits FAN_HCTRL + i of aux (OP_FAN: slot spoke i; OP_SPOKES: spoke i): the
+// gate's control lies outside the tile (work counts only)
+constexpr int FAN_HCTRL = 16;
 
 constexpr uint32_t REMAP_WAVE_LOCAL = 1u;
 constexpr uint32_t IO_BASIS = 16u;
+constexpr uint32_t IO_EXT = 32u;
 
 // One operation of a fused tile pass (104 bytes, every field at least 32 bits
 // wide and naturally aligned so that the kernel reads it with scalar loads).  Its controls are split by
@@ -97,7 +112,8 @@ struct TileArgs {
                                   // physical positions, so every load and store moves
                                   // whole 128-byte lines (non-temporal access pays);
                                   // bit 4 (IO_BASIS): nothing is read, the tiles start as
-                                  // the basis state |0...0> (1 at physical index 0)
+                                  // the basis state |0...0> (1 at physical index 0);
+                                  // bit 5 (IO_EXT): the pass holds OP_LANE or OP_FAN records
     int32_t pad;
     uint8_t sperm[16];            // tile bit b moves to tile bit sperm[b] (io bit 2)
 };

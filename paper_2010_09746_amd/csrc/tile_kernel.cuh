@@ -614,6 +614,77 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
         }
     }
 
+    // x *= (dr, di)
+    static __device__ __forceinline__ void mul(R &x, R &y, R dr, R di)
+    {
+        const R t = x;
+        x = fmadd(dr, t, -di * y);
+        y = fmadd(dr, y, di * t);
+    }
+
+    // An OP_FAN and its spokes (ops[oi + 1 ..]).  The phases of the spokes on
+    // thread bits and outside the tile multiply into one factor per lane, which
+    // the amplitudes whose hub bit is 1 then take in one multiplication;
+    // the spokes on register slots follow one by one.  A Fourier transform's
+    // 26 controlled phases on one target cost about 250 vector instructions
+    // per wavefront this way instead of 26 multiplications of up to 16
+    // amplitudes each: the
+    // transform of 27 qubits, complex128: 17.3 -> 7.0 ms.
+    static __device__ __forceinline__ void fan(int nc, OpPtr ops, int oi, C (&v)[NR], uint32_t fl, uint32_t tbase,
+                                               uint64_t base)
+    {
+        R wr = R(1), wi = R(0);
+        for (int c = 1; c <= nc; ++c) {
+            const OpV sp = fetch(ops, oi + c);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t code = (sp.rmask >> (8 * i)) & 255u;
+                if (code == SPOKE_NONE)
+                    continue;
+                R dr = (R)sp.m[2 * i], di = (R)sp.m[2 * i + 1];
+                if (code & SPOKE_OUT) {
+                    if (((base >> (code & 63u)) & 1u) == 0)
+                        continue;
+                } else {
+                    const bool on = ((tbase >> code) & 1u) != 0;
+                    dr = on ? dr : R(1);
+                    di = on ? di : R(0);
+                }
+                mul(wr, wi, dr, di);
+            }
+        }
+        // the hub's record again: kept through the loop it would cost more
+        // scalar registers than there are
+        const OpV hub = fetch(ops, oi);
+        if (hub.slot == -2 && (base & hub.hbit) == 0)
+            return;
+        // a hub on a thread bit: the other lanes multiply by 1
+        const bool lanes = (tbase & hub.tlane) == hub.tlane;
+        const uint32_t hm = hub.slot >= 0 ? 1u << hub.slot : 0u;
+        if (nc) {
+            wr = lanes ? wr : R(1);
+            wi = lanes ? wi : R(0);
+            const uint32_t hv = hm & ~fl;
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if (((uint32_t)j & hm) == hv)
+                    mul(v[j].x, v[j].y, wr, wi);
+        }
+#pragma unroll
+        for (int q = 0; q < (LOG_R < 4 ? LOG_R : 4); ++q) {
+            if (((hub.rmask >> q) & 1u) == 0)
+                continue;
+            R dr = (R)hub.m[2 * q], di = (R)hub.m[2 * q + 1];
+            dr = lanes ? dr : R(1);
+            di = lanes ? di : R(0);
+            const uint32_t m = hm | (1u << q), mv = m & ~fl;
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if (((uint32_t)j & m) == mv)
+                    mul(v[j].x, v[j].y, dr, di);
+        }
+    }
+
     // Per-tile read-out of the final amplitudes: sum |a|^2 and sum |a|^2 (1 - 2 b)
     // where b is the bit at physical position zpos (the first qubit), reduced
     // over the workgroup in a fixed order and written to out[0..1].
@@ -633,7 +704,8 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
     // |a|^2 over the amplitudes whose bit there is 1, reduced in a fixed order
     // (wavefront butterflies, then the wavefronts in order).
     static constexpr int NV = 1 + LOG_R + LOG_NT;
-    template <bool PF, bool BASIS = false, bool ZB = false, typename A>
+    // EXT: the pass may hold OP_LANE and OP_FAN records (TileArgs::io bit 5).
+    template <bool PF, bool BASIS = false, bool ZB = false, bool EXT = true, typename A>
     static __device__ __forceinline__ void run_range(const A &a, unsigned char *lds, uint64_t t_first, uint64_t t_end,
                                                      uint64_t t_step, Readout ro, double *zparts = nullptr,
                                                      uint64_t zstride = 0)
@@ -750,7 +822,7 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
 #pragma unroll
                     for (int q = 0; q < LOG_R; ++q)
                         so.o[q] = q == slot ? o_new : so.o[q];
-                } else if (kind == OP_LANE) {
+                } else if (EXT && kind == OP_LANE) {
                     dispatch_lane_gate(cur.tlane, tid, v, cur.m);
                 } else if ((base & cur.hmask) == cur.hmask) {
                     const uint32_t rm = cur.rmask, lm = cur.lmask;
@@ -780,6 +852,8 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
                             v[j].x = flip_sign(v[j].x, sj);
                             v[j].y = flip_sign(v[j].y, sj);
                         }
+                    } else if (EXT && kind == OP_FAN) {
+                        fan((int)(cur.aux & 255u), ops, oi, v, fl, tbase, base);
                     } else {  // OP_DIAG: target on register slot `slot`, thread bit tlane, or outside (hbit)
                         R d0r = (R)cur.m[0], d0i = (R)cur.m[1], d1r = (R)cur.m[2], d1i = (R)cur.m[3];
                         // lanes outside the thread-bit controls multiply by 1
@@ -963,12 +1037,17 @@ inline void check_no_static_lds(const void *fn, const char *what)
 // blockIdx.y * gridDim.x + blockIdx.x: a grid holds fewer than 2^32 threads
 // per dimension, so launches of more tiles use rows of workgroups.
 // STREAM: non-temporal loads and stores (TileArgs::io bit 3: whole lines).
-template <typename R, int LOG_NT, int LOG_R, bool STREAM>
+// EXT: with the code of the less frequent records (TileArgs::io bit 5); passes
+// without them run the smaller kernel, which is faster on everything else
+// (29 qubits complex64, 50 layers: 143.4 with, 140.0 ms without; 30 qubits
+// complex128, 40 layers: 354 and 350 ms).
+template <typename R, int LOG_NT, int LOG_R, bool STREAM, bool EXT>
 __global__ __launch_bounds__(1 << LOG_NT) void k_tile(TileArgs a)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const uint64_t t = (uint64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    TileKernel<R, LOG_NT, LOG_R, true, STREAM>::template run_range<false, true>(a, lds_raw, t, t + 1, 1, {nullptr, 0});
+    TileKernel<R, LOG_NT, LOG_R, true, STREAM>::template run_range<false, true, false, EXT>(a, lds_raw, t, t + 1, 1,
+                                                                                        {nullptr, 0});
 }
 
 // The same pass with the ZB read-out of every tile into zparts.
@@ -982,12 +1061,12 @@ __global__ __launch_bounds__(1 << LOG_NT) void k_tile_z(TileArgs a, double *zpar
         a, lds_raw, t, t + 1, 1, {nullptr, 0}, zparts, (uint64_t)gridDim.x * gridDim.y);
 }
 
-template <typename R, int LOG_NT, int LOG_R, bool STREAM, bool ZB>
+template <typename R, int LOG_NT, int LOG_R, bool STREAM, bool ZB, bool EXT>
 void launch_tile_kernel(const TileArgs &a, uint64_t n_tiles, double *zparts, hipStream_t st)
 {
     constexpr size_t bytes = TileKernel<R, LOG_NT, LOG_R>::LDS_BYTES;
     const void *fn = ZB ? reinterpret_cast<const void *>(&k_tile_z<R, LOG_NT, LOG_R, STREAM>)
-                        : reinterpret_cast<const void *>(&k_tile<R, LOG_NT, LOG_R, STREAM>);
+                        : reinterpret_cast<const void *>(&k_tile<R, LOG_NT, LOG_R, STREAM, EXT>);
     // once per process (a thread-safe static initialisation); a failure
     // throws, and the next launch tries again
     static const bool ready = [fn] {
@@ -1011,21 +1090,24 @@ void launch_tile_kernel(const TileArgs &a, uint64_t n_tiles, double *zparts, hip
         hipLaunchKernelGGL((k_tile_z<R, LOG_NT, LOG_R, STREAM>), dim3((unsigned)row, (unsigned)(n_tiles / row)),
                            dim3(1 << LOG_NT), bytes, st, a, zparts);
     else
-        hipLaunchKernelGGL((k_tile<R, LOG_NT, LOG_R, STREAM>), dim3((unsigned)row, (unsigned)(n_tiles / row)),
+        hipLaunchKernelGGL((k_tile<R, LOG_NT, LOG_R, STREAM, EXT>), dim3((unsigned)row, (unsigned)(n_tiles / row)),
                            dim3(1 << LOG_NT), bytes, st, a);
     check_launch("tile pass");
 }
 
 // MODE 0: plain loads and stores; 1: non-temporal (passes over whole 128-byte
-// lines, TileArgs::io bit 3); 2: non-temporal with the per-tile read-out.
+// lines, TileArgs::io bit 3) without OP_LANE and OP_FAN records; 2:
+// non-temporal with the per-tile read-out; 3: non-temporal with those records.
 // Each mode is instantiated in a translation unit of its own, so that the
-// three sets compile in parallel.
+// four sets compile in parallel.
 template <typename R, int LOG_NT, int LOG_R, int MODE>
 void launch_tile_inst(const TileArgs &a, uint64_t n_tiles, double *zparts, hipStream_t st)
 {
     if (MODE != 0 && !(a.io & 8u))
         fail(QS_ERR_UNSUPPORTED, "non-temporal tile pass over partial lines");
-    launch_tile_kernel<R, LOG_NT, LOG_R, MODE != 0, MODE == 2>(a, n_tiles, zparts, st);
+    if (MODE == 1 && (a.io & IO_EXT))
+        fail(QS_ERR_UNSUPPORTED, "tile pass with lane gates or phase fans in the kernel without them");
+    launch_tile_kernel<R, LOG_NT, LOG_R, MODE != 0, MODE == 2, MODE != 1>(a, n_tiles, zparts, st);
 }
 
 // Dispatch over the instantiated shapes: 2^6..2^10 threads, 2..32 amplitudes
