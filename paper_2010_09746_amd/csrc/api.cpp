@@ -1090,21 +1090,34 @@ qs_status qs_read_state(qs_state *s, double *out)
         need(s != nullptr && out != nullptr, "NULL argument");
         need(s->n <= 30, "qs_read_state is limited to n <= 30");
         const uint64_t N = 1ull << s->n;
-        std::vector<unsigned char> raw(s->bytes);
-        hipchk(hipMemcpyAsync(raw.data(), s->buf, s->bytes, hipMemcpyDeviceToHost, s->stream), "hipMemcpyAsync");
-        hipchk(hipStreamSynchronize(s->stream), "hipStreamSynchronize");
-        for (uint64_t i = 0; i < N; ++i) {
-            const uint64_t j = phys_index(i, s->sigma);
-            if (s->dt == QS_C64) {
-                const float *f = reinterpret_cast<const float *>(raw.data());
-                out[2 * i] = f[2 * j];
-                out[2 * i + 1] = f[2 * j + 1];
-            } else {
-                const double *d = reinterpret_cast<const double *>(raw.data());
-                out[2 * i] = d[2 * j];
-                out[2 * i + 1] = d[2 * j + 1];
+        bool identity = s->dt == QS_C128;
+        for (int q = 0; q < s->n; ++q)
+            identity = identity && s->sigma[q] == q;
+        if (identity) {
+            hipchk(hipMemcpyAsync(out, s->buf, s->bytes, hipMemcpyDeviceToHost, s->stream), "hipMemcpyAsync");
+            hipchk(hipStreamSynchronize(s->stream), "hipStreamSynchronize");
+            return;
+        }
+        // put in logical order and FP64 on the device, up to 2^20 amplitudes
+        // (16 MiB of the state's read-out workspace) at a time
+        // (less when the device has no room for that)
+        uint64_t chunk = std::min<uint64_t>(N, 1ull << 20);
+        for (;;) {
+            try {
+                ensure_work(s, 2 * chunk);
+                break;
+            } catch (const Error &) {
+                if (chunk <= 1024)
+                    throw;
+                chunk >>= 2;
             }
         }
+        for (uint64_t i = 0; i < N; i += chunk) {
+            launch_logical(s->buf, s->dt, s->n, s->sigma, i, chunk, s->d_work, s->stream);
+            hipchk(hipMemcpyAsync(out + 2 * i, s->d_work, 2 * chunk * sizeof(double), hipMemcpyDeviceToHost, s->stream),
+                   "hipMemcpyAsync");
+        }
+        hipchk(hipStreamSynchronize(s->stream), "hipStreamSynchronize");
     });
 }
 

@@ -85,6 +85,11 @@ void launch_zfold(const double *parts, uint64_t tiles, int nv, int n, const ZFol
 void launch_gather(const void *state, qs_dtype dt, const uint64_t *idx_dev, int64_t count,
                    double *out_dev, hipStream_t st);
 
+// Amplitudes [i0, i0 + count) in logical order (qubit q at position sigma[q])
+// as FP64 pairs into out_dev; i0 a multiple of 256.
+void launch_logical(const void *state, qs_dtype dt, int n, const std::vector<int> &sigma, uint64_t i0, uint64_t count,
+                    double *out_dev, hipStream_t st);
+
 // Overlap of two states of n qubits: b is read at the physical index whose bit
 // map_b[p] is bit p of a's index (identity when the placements agree).
 // out_dev: [re <a|b>, im <a|b>, <a|a>, <b|b>, max |a - b|].

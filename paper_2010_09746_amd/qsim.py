@@ -399,9 +399,9 @@ def qs_read_amplitudes(h: int, idx) -> np.ndarray:
 
 
 def qs_read_state(h: int, n: int) -> np.ndarray:
-    out = np.zeros(2 << n, dtype=np.float64)
+    out = np.empty(1 << n, dtype=np.complex128)  # (re, im) pairs, as the library writes them
     _chk(load().qs_read_state(h, out.ctypes.data))
-    return out[0::2] + 1j * out[1::2]
+    return out
 
 
 def qs_expect_z(h: int, n: int) -> np.ndarray:

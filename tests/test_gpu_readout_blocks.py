@@ -47,3 +47,14 @@ def test_sums_at_block_edges(n, dt):
             loss, diff = a.fidelity(b)
             assert abs(loss - want) <= 2.0 ** -42
             assert abs(diff - far) <= 2.0 ** -48 * far
+
+
+@pytest.mark.parametrize("dt", ["c64", "c128"])
+@pytest.mark.parametrize("n", [1, 2, 7, 8, 9, 10, 11, 19, 20, 21, 22])
+def test_whole_state_in_logical_order(n, dt):
+    print("whole state", n, dt, flush=True)
+    a, x = _filled(n, dt, n)
+    want = x.cpu().numpy()
+    for sigma in (list(range(n)), list(range(n))[::-1], [int(v) for v in np.random.default_rng(n).permutation(n)]):
+        a.permute(sigma)
+        assert np.array_equal(a.to_numpy(), want)
