@@ -395,7 +395,8 @@ qs_status qs_synchronize(qs_state *s);
  *              2^(k - 8) amplitudes each)
  *   max_fuse   gates per tile pass bound (0 = none)
  *   wg_per_cu  workgroups per compute unit of the persistent launch (0 = 4)
- *   chunk      tiles per work item (0 = 1)
+ *   chunk      largest number of tiles per work item (0 = 1); items are smaller
+ *              where larger ones would leave compute units idle
  *   use_graph  batch: 1 = capture the run once in a HIP graph and replay it
  *   wait_ms    batch: a work item gives up waiting for its circuit's previous
  *              pass after this long (0 = 2000); the run then reports
@@ -422,7 +423,7 @@ typedef struct {
 /* Compile count circuits (circuit c: n_qubits[c] qubits, gates[c] a host array
  * of n_gates[c] gates) for execution together.  Each circuit is compiled with
  * its own tile size (see qs_batch_opts.k_tile) and its tile passes become work
- * items (chunk tiles each).  A run is one persistent launch: workgroups take
+ * items (at most chunk tiles each).  A run is one persistent launch: workgroups take
  * items in a fixed order by ticket, and an item whose circuit's previous pass
  * is not complete waits for it (the order puts every pass's items after all
  * items of the pass before it, which guarantees progress).  The first pass of

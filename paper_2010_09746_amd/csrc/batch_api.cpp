@@ -119,7 +119,6 @@ void plan_batch(int count, const int *n, const qs_gate *const *gates, const int6
     }
     // work items: level by level; within a level, circuits by the amplitudes
     // their remaining passes touch (most first)
-    const uint32_t chunk = (uint32_t)std::max(1, o.chunk);
     size_t max_np = 0;
     for (auto &v : bp.circ_passes)
         max_np = std::max(max_np, v.size());
@@ -139,6 +138,11 @@ void plan_batch(int count, const int *n, const qs_gate *const *gates, const int6
             const double lb = lvl < bp.circ_passes[b].size() ? left[b][lvl] : -1.0;
             return la > lb;
         });
+        uint64_t tiles = 0;
+        for (int c = 0; c < count; ++c)
+            if (lvl < bp.circ_passes[c].size())
+                tiles += bp.passes[bp.circ_passes[c][lvl]].tiles;
+        const uint32_t chunk = tiles_per_item(tiles, o.chunk);
         for (int c : order) {
             if (lvl >= bp.circ_passes[c].size())
                 continue;

@@ -77,6 +77,23 @@ struct QueueArgs {
     uint64_t wait_ticks;       // longest wait for a dependency, in 100 MHz clock ticks
 };
 
+// Tiles per work item where `tiles` tiles can run together: the caller's bound
+// (options' chunk), but small enough for 5 items per compute unit, about what
+// is resident.  With fewer items whole compute units idle while others work
+// through several tiles, and the next pass waits for the last of them; with
+// more than a few rounds of items a larger item costs fewer tickets and cache
+// write-backs.  One run of a batch (complex64, tiles of 2^12) by tiles per
+// item 1, 2, 4, 8: 64 circuits of 10-20 qubits (about 3000 tiles per level)
+// 2.08, 2.07, 6.87, 9.41 ms; 30 circuits of 10-21 qubits (2600) 4.09, 3.09,
+// 4.14, 16.9 ms; 90 of 10-16 qubits (420) 3.83, 3.99, 5.76, 7.63 ms; 200 of
+// 10-22 qubits (31000) 39.5, 26.9, 22.8, 22.2 ms.
+inline uint32_t tiles_per_item(uint64_t tiles, int32_t chunk)
+{
+    constexpr uint64_t ITEMS = 5 * 256;
+    const uint64_t most = chunk > 1 ? (uint64_t)chunk : 1, fit = tiles / ITEMS;
+    return (uint32_t)(fit < 1 ? 1 : fit < most ? fit : most);
+}
+
 // A range of tiles of one pass: the unit of work of a level launch.
 struct BatchItem {
     uint32_t pass, t0, t1, pad;

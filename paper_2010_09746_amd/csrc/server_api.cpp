@@ -405,13 +405,18 @@ qs_status qs_server_step_launch(qs_server *s, int *n_running)
         if (s->steps_pending >= MAX_STEPS_IN_FLIGHT)
             fail(QS_ERR_STATE, "two steps in flight: wait for the older one first");
         SStep &step = s->steps[(s->step_head + s->steps_pending) % MAX_STEPS_IN_FLIGHT];
-        const uint32_t chunk = (uint32_t)std::max(1, s->opts.chunk);
+        // the passes of the shared launch and their items
+        auto shared = [&](const SReq &r) {
+            const uint64_t nt = 1ull << (r.n - s->K);
+            return r.cur < r.np && !(s->solo_tiles && nt >= s->solo_tiles) ? nt : 0ull;
+        };
+        uint64_t tiles = 0;
+        for (int64_t id : s->active)
+            tiles += shared(s->reqs.at(id));
+        const uint32_t chunk = tiles_per_item(tiles, s->opts.chunk);
         size_t need = 0;
-        for (int64_t id : s->active) {
-            const SReq &r = s->reqs.at(id);
-            if (r.cur < r.np)
-                need += ((1ull << (r.n - s->K)) + chunk - 1) / chunk;
-        }
+        for (int64_t id : s->active)
+            need += (shared(s->reqs.at(id)) + chunk - 1) / chunk;
         ensure_items(step, need + 1);
         size_t ni = 0;
         int running = 0;
