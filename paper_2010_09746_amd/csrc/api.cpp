@@ -489,6 +489,15 @@ void run_program_with_ops(qs_state *s, const Program &p, const TileOp *d_ops)
     s->sigma = p.sigma_final;
 }
 
+const Program &usual_shape(const Program &p, Program &tmp)
+{
+    if (!p.small_shape)
+        return p;
+    compile_program(p.src.data(), (int64_t)p.src.size(), p.n, p.dt, p.sigma0.data(), p.opts, tmp, {},
+                    p.costed ? &p.costs : nullptr);
+    return tmp;
+}
+
 void *state_stream(const qs_state *s) { return s->stream; }
 int state_device(const qs_state *s) { return s->dev; }
 
@@ -683,7 +692,19 @@ qs_status compile_entry(const qs_gate *gates, int64_t n_gates, int n, qs_dtype d
             check_costs(*costs);
         auto *p = new qs_program();
         try {
-            compile_program(gates, n_gates, n, dt, sigma0, o, p->p, {}, costs);
+            compile_program(gates, n_gates, n, dt, sigma0, o, p->p, {}, costs, true, true);
+            // a small state's shape needs more records: where they pass the
+            // limit of qs_run_program_noalloc the usual shape stays
+            if (p->p.small_shape && p->p.ops.size() > (size_t)QS_NOALLOC_MAX_OPS) {
+                p->p = Program();
+                compile_program(gates, n_gates, n, dt, sigma0, o, p->p, {}, costs);
+            }
+            if (p->p.small_shape) {
+                p->p.src.assign(gates, gates + n_gates);
+                p->p.costed = costs != nullptr;
+                if (costs)
+                    p->p.costs = *costs;
+            }
         } catch (...) {
             delete p;
             throw;
@@ -992,7 +1013,7 @@ qs_status run_circuit_entry(qs_state *s, const qs_gate *gates, int64_t n_gates, 
         };
         if (o.form == QS_FORM_PASS) {
             try {
-                compile_program(gates, n_gates, s->n, s->dt, s->sigma.data(), o, p, progress, costs);
+                compile_program(gates, n_gates, s->n, s->dt, s->sigma.data(), o, p, progress, costs, true, true);
             } catch (...) {
                 // launches already enqueued read the op tables: let them
                 // finish before the error is reported (the state then holds a

@@ -484,6 +484,22 @@ int pass_reg_bits(int k, qs_dtype dt)
     return 4;
 }
 
+int small_state_reg_bits(int n, int k, qs_dtype dt)
+{
+    // Up to 2^21 amplitudes a pass has at most two wavefronts per SIMD with 16
+    // amplitudes per thread, and the time of a wavefront's own chain of
+    // instructions is what counts: more, shorter wavefronts are faster although
+    // they re-lay registers out more often.  Measured at 20 layers, k = 12, 16
+    // against 8 amplitudes per thread: complex64 14 qubits 189, 159 us, 18: 263,
+    // 224, 21: 354, 342, 22: 486, 535; complex128 14 qubits 181, 158, 18: 257, 226,
+    // 21: 406, 377, 22: 620, 666 (the same line at k = 9, 10, 11).  A
+    // complex64 state that is one tile runs alone on its compute unit: 4
+    // amplitudes per thread (10 qubits 129, 107, 94 us with 16, 8, 4).
+    if (n > 21)
+        return pass_reg_bits(k, dt);
+    return dt == QS_C64 && n == k ? 2 : 3;
+}
+
 void tile_shape(int k, qs_dtype dt, int reg_bits_opt, int *log_r, int *log_nt)
 {
     int lr = reg_bits_opt > 0 ? reg_bits_opt : pass_reg_bits(k, dt);
@@ -1544,7 +1560,7 @@ void tile_args_identity(int k, int log_nt, int log_r, TileArgs &a)
 
 void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int *sigma0_in,
                      const qs_run_opts &o, Program &p, const std::function<void(Program &)> &progress,
-                     const qs_pass_costs *costs, bool fans)
+                     const qs_pass_costs *costs, bool fans, bool small_shapes)
 {
     auto t0 = std::chrono::steady_clock::now();
     if (n < 1 || n > MAX_COMPILE_QUBITS)
@@ -1639,8 +1655,14 @@ void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int
         // segments gate by gate
         const bool tiled = k >= MIN_TILE_BITS && (size_t(dt == QS_C64 ? 8 : 16) << k) <= MAX_TILE_BYTES;
         int log_r = 0, log_nt = 0;
-        if (tiled)
+        if (tiled) {
             tile_shape(k, dt, o.reg_bits, &log_r, &log_nt);
+            if (small_shapes && o.reg_bits <= 0) {
+                const int usual = log_r;
+                tile_shape(k, dt, small_state_reg_bits(n, k, dt), &log_r, &log_nt);
+                p.small_shape = log_r != usual;
+            }
+        }
         std::vector<int> spass = p.sigma0;
         size_t i = 0;
         // reduced one-qubit updates only where tile passes run them

@@ -188,6 +188,12 @@ struct Program {
     std::vector<Launch> launches;
     std::vector<TileOp> ops;
     qs_program_stats stats{};
+    // lowered with another tile shape than the usual one (small states); then
+    // the source is kept, for callers that need the usual shape
+    bool small_shape = false;
+    std::vector<qs_gate> src;
+    bool costed = false;
+    qs_pass_costs costs{};
     // device copy of ops (per device, uploaded on first run)
     int dev = -1;
     TileOp *d_ops = nullptr;
@@ -197,10 +203,12 @@ struct Program {
 // iteration, once the launches of every completed segment are in p.launches
 // (and their operations in p.ops); launches already there never change.
 // Without fans, controlled phases stay one operation each (for the batching
-// form's kernel, which has no code for OP_FAN).
+// form's kernel, which has no code for OP_FAN).  With small_shapes and no
+// reg_bits asked for, small states get the register bits of
+// small_state_reg_bits (p.small_shape: they differ from the usual ones).
 void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int *sigma0,
                      const qs_run_opts &o, Program &p, const std::function<void(Program &)> &progress = {},
-                     const qs_pass_costs *costs = nullptr, bool fans = true);
+                     const qs_pass_costs *costs = nullptr, bool fans = true, bool small_shapes = false);
 
 }  // namespace qsim
 
@@ -219,12 +227,18 @@ void tile_args_from_launch(const Launch &L, TileArgs &a);
 void tile_args_identity(int k, int log_nt, int log_r, TileArgs &a);
 void tile_args_for_positions(const std::vector<int> &pos, int log_nt, int log_r, TileArgs &a);
 
+// p itself, or compiled again into tmp with the usual tile shape when p has
+// that of a small state
+const Program &usual_shape(const Program &p, Program &tmp);
+
 // choose register bits / threads for a tile of k bits
 // Tile shape: 2^log_r amplitudes per thread (reg_bits_opt, or pass_reg_bits
 // when 0), clamped to 64..1024 threads.
 void tile_shape(int k, qs_dtype dt, int reg_bits_opt, int *log_r, int *log_nt);
 // register bits of a tile when none are asked for (measured)
 int pass_reg_bits(int k, qs_dtype dt);
+// the same for one state of n qubits run by itself
+int small_state_reg_bits(int n, int k, qs_dtype dt);
 
 // ---------------------------------------------------------------------------
 // state access for entry points defined outside api.cpp

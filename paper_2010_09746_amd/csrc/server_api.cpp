@@ -308,7 +308,9 @@ qs_status qs_server_admit(qs_server *s, const qs_program *pp, void *state_buf, s
     return guard([&] {
         if (!s || !pp || !state_buf || !request_id || count < 0 || count > s->max_samples || (count && !samples))
             fail(QS_ERR_ARG, "bad arguments");
-        const Program &p = pp->p;
+        // the shared launch has one tile shape, the usual one
+        Program tmp;
+        const Program &p = usual_shape(pp->p, tmp);
         const int n = p.n;
         const size_t eb = s->dt == QS_C64 ? 8 : 16;
         const size_t bytes = eb << n;
