@@ -767,6 +767,7 @@ qs_status qs_program_op_counts(const qs_program *p, double *out, int cap)
                     if (o.kind == OP_REMAP) {
                         c[QS_OPC_REMAP] += 1;
                         c[QS_OPC_REMAP_WAVE] += (o.aux & REMAP_WAVE_LOCAL) ? 1 : 0;
+                        c[QS_OPC_DISPATCH] += (double)(o.aux >> REMAP_COUNT);  // CNOTs it carries out
                         continue;
                     }
                     if (o.kind == OP_SHEAR2) {

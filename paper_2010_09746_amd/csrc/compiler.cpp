@@ -1259,6 +1259,118 @@ void fuse_phase_fans(std::vector<TileOp> &ops, size_t begin)
     ops.resize(w);
 }
 
+// CNOTs carried out by the next re-layout's addresses.
+//
+// A CNOT moves the amplitude at tile index i to i XOR the target bit where the
+// control bit is 1: a linear map of the index.  A re-layout writes every amplitude to
+// LDS at its index anyway, so a CNOT that may wait until then costs nothing
+// but other write addresses: it may if no operation between the two touches its
+// target or acts non-diagonally on its control.  The target is a register
+// slot, so M, the map of all CNOTs of one re-layout, changes register bits of
+// the old layout only: M of a slot bit is a constant per slot (words
+// REMAP_IMG + s), M of a thread's part differs from it by a constant for each
+// thread bit that is a control (words REMAP_LANE + e), at most REMAP_LANES of
+// them; the wavefront bits keep their tile bits.  55% of the exchanges of the
+// CNOT-only random family go this way (26 qubits), 20% at one CNOT in three,
+// few in layered circuits (a one-qubit gate follows each CNOT in the same
+// layout).  20 qubits complex64, CNOTs only: 390 -> 312 us; 26 qubits, 70% CNOTs:
+// 7.91 -> 7.51 ms; 30%: 6.34 -> 6.20 ms.
+void absorb_exchanges(std::vector<TileOp> &ops, size_t begin, int k, int log_r)
+{
+    std::vector<size_t> rl;
+    for (size_t i = begin; i < ops.size(); ++i) {
+        if (ops[i].kind == OP_REMAP)
+            rl.push_back(i);
+        if (ops[i].kind == OP_LANE)
+            return;  // names thread bits, not tile bits
+    }
+    std::vector<char> gone(ops.size(), 0);
+    bool any_gone = false;
+    for (size_t x = 1; x < rl.size(); ++x) {
+        const TileOp &old = ops[rl[x - 1]];
+        auto bit_of = [&](int slot) { return (int)((old.rmask >> (4 * slot)) & 15u); };
+        auto slot_bits = [&](uint32_t slots) {
+            uint32_t m = 0;
+            for (int s = 0; s < log_r; ++s)
+                if ((slots >> s) & 1u)
+                    m |= 1u << bit_of(s);
+            return m;
+        };
+        uint32_t regs = slot_bits((1u << log_r) - 1u), touched = 0, nondiag = 0, lane_ctrl = 0;
+        std::vector<std::pair<int, int>> cnots;  // (control, target) tile bits, last first
+        for (size_t i = rl[x]; i-- > rl[x - 1] + 1;) {
+            const TileOp &o = ops[i];
+            uint32_t ctrl = slot_bits(o.rmask) | o.lmask, tgt = 0, diag = 0;
+            switch (o.kind) {
+            case OP_SHEAR2:
+                tgt |= 1u << bit_of((int)(o.aux & 255u));
+                [[fallthrough]];
+            case OP_SHEAR:
+            case OP_U:
+            case OP_X:
+                tgt |= 1u << bit_of(o.slot);
+                break;
+            case OP_PHASE:
+                diag = 1u << bit_of(o.slot);
+                break;
+            case OP_DIAG:
+            case OP_FAN:
+                diag = (o.slot >= 0 ? 1u << bit_of(o.slot) : 0u) | o.tlane;
+                break;
+            case OP_SPOKES:
+                ctrl = 0;
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t code = (o.rmask >> (8 * e)) & 255u;
+                    if (!(code & SPOKE_OUT))
+                        diag |= 1u << code;
+                }
+                break;
+            default:
+                break;
+            }
+            if (o.kind == OP_X && o.hmask == 0 && __builtin_popcount(ctrl) == 1 && !(tgt & touched) &&
+                !(ctrl & nondiag) &&
+                __builtin_popcount(lane_ctrl | (ctrl & ~regs)) <= REMAP_LANES) {
+                cnots.emplace_back(__builtin_ctz(ctrl), __builtin_ctz(tgt));
+                lane_ctrl |= ctrl & ~regs;
+                gone[i] = 1;
+                any_gone = true;
+                continue;
+            }
+            touched |= ctrl | tgt | diag;
+            nondiag |= tgt;
+        }
+        if (cnots.empty())
+            continue;
+        // images of the tile bits under the CNOTs in program order
+        uint32_t img[16];
+        for (int b = 0; b < k; ++b)
+            img[b] = 1u << b;
+        for (size_t c = cnots.size(); c-- > 0;)
+            for (int b = 0; b < k; ++b)
+                if ((img[b] >> cnots[c].first) & 1u)
+                    img[b] ^= 1u << cnots[c].second;
+        TileOp &r = ops[rl[x]];
+        uint32_t words[16];
+        std::memcpy(words, r.m, sizeof words);
+        for (int s = 0; s < log_r; ++s)
+            words[REMAP_IMG + s] = lds_swizzle(img[bit_of(s)], k);
+        int e = 0;
+        for (int b = 0; b < k; ++b)
+            if (!((regs >> b) & 1u) && img[b] != (1u << b))
+                words[REMAP_LANE + e++] = (img[b] ^ (1u << b)) | ((uint32_t)b << 16);
+        std::memcpy(r.m, words, sizeof words);
+        r.aux |= REMAP_CNOTS | ((uint32_t)cnots.size() << REMAP_COUNT);
+    }
+    if (!any_gone)
+        return;
+    size_t w = begin;
+    for (size_t i = begin; i < ops.size(); ++i)
+        if (!gone[i])
+            ops[w++] = ops[i];
+    ops.resize(w);
+}
+
 // Wavefront-local re-layouts.  The thread-id bits above the lane bits (6 and
 // up) number the wavefronts of a workgroup.  A re-layout that leaves the same
 // tile bits on them moves amplitudes only between the lanes and registers of
@@ -1379,7 +1491,7 @@ void assign_wave_bits(std::vector<TileOp> &ops, size_t begin, int k, int log_r, 
         for (size_t i = 0; i < order.size(); ++i)
             lanes |= (uint64_t)order[i] << (4 * i);
         op.hbit = lanes;
-        op.aux = keep ? REMAP_WAVE_LOCAL : 0u;
+        op.aux = (op.aux & ~REMAP_WAVE_LOCAL) | (keep ? REMAP_WAVE_LOCAL : 0u);
     }
 }
 
@@ -1738,6 +1850,7 @@ void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int
                     p.stats.n_remaps += schedule_segment(lg, g, gi, k, log_r, p.ops, pf, lane_bits, lane_eager);
                     if (fans)
                         fuse_phase_fans(p.ops, (size_t)L.op_begin);
+                    absorb_exchanges(p.ops, (size_t)L.op_begin, k, log_r);
                     // lane gates name thread bits of the ascending map
                     if (lane_bits == 0)
                         assign_wave_bits(p.ops, (size_t)L.op_begin, k, log_r, log_nt, direct_low_bits(dt),

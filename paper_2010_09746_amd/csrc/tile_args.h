@@ -50,6 +50,14 @@ constexpr uint32_t SPOKE_OUT = 0x80u, SPOKE_NONE = 0xffu;
 constexpr int FAN_HCTRL = 16;
 
 constexpr uint32_t REMAP_WAVE_LOCAL = 1u;
+// OP_REMAP with aux & REMAP_CNOTS also carries out CNOTs (their number at bits
+// REMAP_COUNT.. of aux) by writing to LDS at the mapped tile index: word
+// REMAP_IMG + s of m is the LDS slot of the image of the old layout's slot bit
+// s; word REMAP_LANE + e (e < REMAP_LANES) names a tile bit on the threads
+// (bits 16..) whose image has the tile bits in its low 16 bits besides itself (0:
+// no entry)
+constexpr uint32_t REMAP_CNOTS = 2u;
+constexpr int REMAP_COUNT = 8, REMAP_IMG = 5, REMAP_LANE = 10, REMAP_LANES = 4;
 constexpr uint32_t IO_BASIS = 16u;
 constexpr uint32_t IO_EXT = 32u;
 

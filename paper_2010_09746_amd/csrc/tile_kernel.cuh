@@ -548,7 +548,7 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
         uint32_t rmask, lmask, tlane, aux;
         uint64_t hmask, hbit;
         double m[8];
-        uint32_t w[6];  // the first words of m (OP_REMAP: LDS slots of the new layout's slot bits)
+        uint32_t w[14];  // the first words of m (OP_REMAP)
     };
     // The record as three wide scalar loads (64 + 32 + 8 bytes) issued
     // together, so that one wait covers the whole operation.
@@ -584,6 +584,9 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
 #pragma unroll
         for (int q = 0; q < 6; ++q)
             o.w[q] = a[10 + q];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            o.w[6 + q] = b[q];
         return o;
     }
 
@@ -808,6 +811,16 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
                 } else if (kind == OP_REMAP) {
                     const SlotOffs so2 = offs_of(cur.w);
                     const uint32_t tbase2 = lane_bits(cur.hbit, tid);
+                    if (cur.aux & REMAP_CNOTS) {
+                        // written at the index the CNOTs map it to
+                        so = offs_of(cur.w + REMAP_IMG);
+                        const uint32_t tb = tbase;
+#pragma unroll
+                        for (int e = 0; e < REMAP_LANES; ++e) {
+                            const uint32_t x = cur.w[REMAP_LANE + e];
+                            tbase ^= ((tb >> (x >> 16)) & 1u) ? (x & 0xffffu) : 0u;
+                        }
+                    }
                     relayout(lds, v, tbase, so, fl, tbase2, so2, (cur.aux & REMAP_WAVE_LOCAL) != 0);
                     so = so2;
                     tbase = tbase2;
