@@ -262,8 +262,9 @@ qs_status qs_program_get_stats(const qs_program *p, qs_program_stats *out);
  *   QS_OPC_U .. QS_OPC_REMAP  operations inside tile passes, each weighted by
  *                      the fraction of tiles that execute it (2^-h for h
  *                      control positions outside the tile)
- *   QS_OPC_DISPATCH    fetched operations that move no data on a tile: uniform
- *                      exchanges (relabels) and skipped conditional operations
+ *   QS_OPC_DISPATCH    operations that move no data on a tile: uniform
+ *                      exchanges (relabels), skipped conditional operations and
+ *                      CNOTs that a re-layout carries out in its addresses
  *   QS_OPC_PLAIN_*     one-gate launches by gate kind
  *   QS_OPC_MOVE        data-movement launches, QS_OPC_MOVE_FRACTION the sum
  *                      of the fractions of amplitudes they move
@@ -281,7 +282,7 @@ enum {
     QS_OPC_X_REG = 3,      /* exchange controlled by register bits */
     QS_OPC_X_LANE = 4,     /* exchange controlled by thread bits */
     QS_OPC_NEG = 5,        /* CZ sign flip */
-    QS_OPC_DIAG = 6,       /* diagonal one-qubit or controlled-diagonal gate */
+    QS_OPC_DIAG = 6,       /* diagonal one-qubit or controlled-diagonal gate (also those run several at once) */
     QS_OPC_REMAP = 7,      /* register re-layout through LDS */
     QS_OPC_DISPATCH = 8,
     QS_OPC_PLAIN_U = 9,

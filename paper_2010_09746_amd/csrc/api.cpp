@@ -313,7 +313,7 @@ void apply_position_map(qs_state *s, const std::vector<int> &pi)
                 a.sperm[b] = (uint8_t)(mine[pos[b]] ? tb[pi[pos[b]]] : b);
             // permuted store; the tile holds the lowest positions, so every
             // load and store moves whole lines (streaming access)
-            a.io = 4u | 8u;
+            a.io = 4u | 8u | IO_EXT;
             a.state = s->buf;
             a.ops = nullptr;
             a.n_ops = 0;

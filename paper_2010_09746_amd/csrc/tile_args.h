@@ -121,7 +121,8 @@ struct TileArgs {
                                   // whole 128-byte lines (non-temporal access pays);
                                   // bit 4 (IO_BASIS): nothing is read, the tiles start as
                                   // the basis state |0...0> (1 at physical index 0);
-                                  // bit 5 (IO_EXT): the pass holds OP_LANE or OP_FAN records
+                                  // bit 5 (IO_EXT): the pass holds OP_LANE or OP_FAN records or
+                                  // permutes its store (bit 2)
     int32_t pad;
     uint8_t sperm[16];            // tile bit b moves to tile bit sperm[b] (io bit 2)
 };

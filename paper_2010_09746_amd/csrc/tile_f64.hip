@@ -1,6 +1,6 @@
 // complex128 instantiations of the fused tile pass over whole 128-byte lines
-// (non-temporal access); passes with lane gates or phase fans go to
-// launch_tile_f64_ext, passes over partial lines to launch_tile_f64_plain
+// (non-temporal access); passes with lane gates, phase fans or a permuted
+// store go to launch_tile_f64_ext, passes over partial lines to launch_tile_f64_plain
 #include "kernels.h"
 #include "tile_kernel.cuh"
 

@@ -1,5 +1,5 @@
 // complex128 instantiations of the fused tile pass over whole 128-byte lines
-// with lane gates and phase fans
+// with lane gates, phase fans and permuted stores
 #include "kernels.h"
 #include "tile_kernel.cuh"
 
