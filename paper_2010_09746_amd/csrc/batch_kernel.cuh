@@ -15,10 +15,13 @@ template <typename R, int LOG_NT, int LOG_R>
 __global__ __launch_bounds__(1 << LOG_NT) void k_batch(BatchArgs b)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    // whole amplitudes per re-layout round: the persistent grid, not LDS,
-    // sets how many workgroups are resident; ordinary (cached) loads and
-    // stores: the states are small and are read again at the next level
-    using TK = TileKernel<R, LOG_NT, LOG_R, false, false>;
+    // Ordinary (cached) loads and stores: the states are small and are read
+    // again at the next level.  Loading the next tile while one is processed
+    // (a second register array, two wavefronts per SIMD) does not pay: items
+    // are single tiles unless there are many, and then more resident workgroups
+    // overlap better (24 served requests of 12-25 qubits 24.8 -> 23.9 ms,
+    // 16 of 12-24 qubits 8.9 -> 8.2 ms without it).
+    using TK = TileKernel<R, LOG_NT, LOG_R, false>;
     using PassPtr = const __attribute__((address_space(4))) BatchPass *;
     using ItemPtr = const __attribute__((address_space(4))) BatchItem *;
     PassPtr passes = (PassPtr)b.passes;
@@ -27,7 +30,7 @@ __global__ __launch_bounds__(1 << LOG_NT) void k_batch(BatchArgs b)
         const uint32_t pi = items[it].pass, t0 = items[it].t0, t1 = items[it].t1;
         const auto &P = passes[pi];
         typename TK::Readout ro{P.last ? b.partials + 2 * (P.part + t0) : nullptr, P.zpos};
-        TK::template run_range<true>(P.t, lds_raw, t0, t1, 1, ro);
+        TK::template run_range<>(P.t, lds_raw, t0, t1, 1, ro);
     }
 }
 
@@ -50,11 +53,7 @@ __global__ __launch_bounds__(1 << LOG_NT) void k_batch(BatchArgs b)
 // sets the abort flag or another wait has given up; the launch then ends
 // early with the error flag set, and the host reports it.
 template <typename R> struct QueueKernel {
-    // one component per re-layout round (LDS holds half a tile): moving
-    // whole amplitudes made the kernel need more registers (complex64: 129
-    // VGPRs, 3 wavefronts per SIMD, instead of 111)
-    static constexpr bool HALF = true;
-    template <int SH> using TK = TileKernel<R, QUEUE_LOG_NT, SH, HALF, false>;
+    template <int SH> using TK = TileKernel<R, QUEUE_LOG_NT, SH, false>;
     static constexpr uint32_t mx(uint32_t a, uint32_t b) { return a > b ? a : b; }
     static constexpr uint32_t TILE_LDS =
         mx(mx(TK<1>::LDS_BYTES, TK<2>::LDS_BYTES), mx(TK<3>::LDS_BYTES, TK<4>::LDS_BYTES));
@@ -137,10 +136,10 @@ __global__ __launch_bounds__(256) void k_batch_queue(QueueArgs q)
         const auto &P = passes[pi];
         double *part = P.last ? q.partials + 2 * (P.part + t0) : nullptr;
         switch (sh) {
-        case 1: QK::template TK<1>::template run_range<false, true, false, false>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
-        case 2: QK::template TK<2>::template run_range<false, true, false, false>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
-        case 3: QK::template TK<3>::template run_range<false, true, false, false>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
-        default: QK::template TK<4>::template run_range<false, true, false, false>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
+        case 1: QK::template TK<1>::template run_range<true, false, false>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
+        case 2: QK::template TK<2>::template run_range<true, false, false>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
+        case 3: QK::template TK<3>::template run_range<true, false, false>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
+        default: QK::template TK<4>::template run_range<true, false, false>(P.t, lds_raw, t0, t1, 1, {part, P.zpos}); break;
         }
         // every wavefront's stores (and read-out partials) have completed
         __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -206,7 +205,7 @@ template <typename R> void launch_batch_queue_t(const QueueArgs &q, int grid, hi
 template <typename R, int LOG_NT, int LOG_R>
 void launch_batch_inst(const BatchArgs &b, int grid, hipStream_t st)
 {
-    constexpr size_t bytes = TileKernel<R, LOG_NT, LOG_R, false, false>::LDS_BYTES;
+    constexpr size_t bytes = TileKernel<R, LOG_NT, LOG_R, false>::LDS_BYTES;
     // once per process (a thread-safe static initialisation); a failure
     // throws, and the next launch tries again
     static const bool ready = [] {

@@ -33,8 +33,7 @@
 //   registers -> HBM  straight from the last layout when its thread bits
 //                     cover the lowest tile bits, else through LDS
 // The pass kernel runs one workgroup per tile; the batching form's persistent
-// workgroups load their next tile into a second register array while the
-// current one is processed.
+// workgroups take tiles one after the other.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -46,7 +45,7 @@
 
 namespace qsim {
 
-template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = true> struct TileKernel {
+template <typename R, int LOG_NT, int LOG_R, bool STREAM = true> struct TileKernel {
     using C = typename Cx<R>::T;
     static constexpr int NT = 1 << LOG_NT, NR = 1 << LOG_R, K = LOG_NT + LOG_R;
     static constexpr uint32_t CB = sizeof(C);  // bytes per amplitude
@@ -54,8 +53,7 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
     // Order the LDS accesses of different lanes.  A single wavefront issues its
     // LDS instructions in order, so only the compiler must be kept from
     // reordering them; several wavefronts wait for their LDS operations and
-    // meet at a barrier.  Neither form waits for outstanding global loads, so
-    // the prefetch of the next tile stays in flight.
+    // meet at a barrier.  Neither form waits for outstanding global stores.
     static __device__ __forceinline__ void lds_sync()
     {
         if constexpr (NT == 64)
@@ -422,11 +420,8 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
     // LDS holds one component (real or imaginary part) of the tile at a time:
     // half the bytes of the tile, so that more workgroups fit a CU.  The
     // read-out reduction needs 2 NT doubles.
-    // With HALF a re-layout moves one component per round and LDS holds half
-    // the tile; otherwise one round moves whole amplitudes (fewer barriers,
-    // for kernels whose residency LDS does not limit).
     static constexpr uint32_t RB = sizeof(R);
-    static constexpr uint32_t EB = HALF ? RB : CB;  // bytes per LDS element of a re-layout
+    static constexpr uint32_t EB = RB;  // bytes per LDS element of a re-layout
     static constexpr uint32_t LDS_BYTES = (EB << K) > 16u * NT ? (EB << K) : 16u * NT;
     // the plain layout: thread bits are tile bits 0..LOG_NT-1, slot bit s is
     // tile bit LOG_NT + s
@@ -439,29 +434,17 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
         return so;
     }
 
-    // element COMP of an amplitude in LDS: 0 real part, 1 imaginary part, 2
-    // both (a two-element vector, one LDS access)
-    using V2 = R __attribute__((ext_vector_type(2)));
+    // element COMP of an amplitude in LDS: 0 real part, 1 imaginary part
     template <int COMP> static __device__ __forceinline__ void put(uint32_t addr, const C &c)
     {
-        if constexpr (COMP == 0)
-            *at<R>(addr) = c.x;
-        else if constexpr (COMP == 1)
-            *at<R>(addr) = c.y;
-        else
-            *at<V2>(addr) = V2{c.x, c.y};
+        *at<R>(addr) = COMP == 0 ? c.x : c.y;
     }
     template <int COMP> static __device__ __forceinline__ void get(uint32_t addr, C &c)
     {
-        if constexpr (COMP == 0) {
+        if constexpr (COMP == 0)
             c.x = *at<R>(addr);
-        } else if constexpr (COMP == 1) {
+        else
             c.y = *at<R>(addr);
-        } else {
-            const V2 t = *at<V2>(addr);
-            c.x = t.x;
-            c.y = t.y;
-        }
     }
 
     // LDS slot of tile-local index i (lds_swizzle): thread bits placed on
@@ -506,7 +489,7 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
     }
 
     // Re-layout (tbase, so, fl) -> (tbase2, so2, no flips) through LDS, one
-    // component per round with HALF.
+    // component per round.
     // With wave_local the two layouts put the same tile bits on the
     // wavefront-index bits of the thread id: each wavefront reads back only
     // LDS slots it wrote, in order, so only the compiler is kept from
@@ -523,21 +506,14 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
             else
                 lds_sync();
         };
-        if constexpr (HALF) {
-            to_lds<0>(lds, v, tbase, so, fl);
-            sync();
-            from_lds<0>(lds, v, tbase2, so2);
-            sync();
-            to_lds<1>(lds, v, tbase, so, fl);
-            sync();
-            from_lds<1>(lds, v, tbase2, so2);
-            sync();
-        } else {
-            to_lds<2>(lds, v, tbase, so, fl);
-            sync();
-            from_lds<2>(lds, v, tbase2, so2);
-            sync();
-        }
+        to_lds<0>(lds, v, tbase, so, fl);
+        sync();
+        from_lds<0>(lds, v, tbase2, so2);
+        sync();
+        to_lds<1>(lds, v, tbase, so, fl);
+        sync();
+        from_lds<1>(lds, v, tbase2, so2);
+        sync();
     }
 
     using OpPtr = const __attribute__((address_space(4))) TileOp *;
@@ -708,7 +684,7 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
     // (wavefront butterflies, then the wavefronts in order).
     static constexpr int NV = 1 + LOG_R + LOG_NT;
     // EXT: the pass may hold OP_LANE and OP_FAN records (TileArgs::io bit 5).
-    template <bool PF, bool BASIS = false, bool ZB = false, bool EXT = true, typename A>
+    template <bool BASIS = false, bool ZB = false, bool EXT = true, typename A>
     static __device__ __forceinline__ void run_range(const A &a, unsigned char *lds, uint64_t t_first, uint64_t t_end,
                                                      uint64_t t_step, Readout ro, double *zparts = nullptr,
                                                      uint64_t zstride = 0)
@@ -735,9 +711,6 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
         auto pbit_ld = [&](int s) { return 1ull << a.ld_reg[s]; };
         auto pbit_st = [&](int s) { return 1ull << a.st_reg[s]; };
 
-        // v holds the tile being processed; the next tile of the workgroup is
-        // loaded into w while v is processed and moves into v after v's
-        // stores are issued, so the wait for it never waits for those stores
         C v[NR];
         auto load = [&](C(&dst)[NR], uint64_t tile) {
             const C *src = st + tile_base(a, tile) + lane_ld;
@@ -764,27 +737,13 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
                 }
             });
         };
-        if constexpr (PF) {
-            if (t_first < t_end) {
-                load(v, t_first);
-                touch_records(ops, n_ops, tid);
-            }
-            // wait for the first tile here, so that the loop's own waits are only
-            // those for the prefetched tile (vmcnt(0): expcnt and lgkmcnt left at
-            // their maxima)
-            __builtin_amdgcn_s_waitcnt(0x0F70);
-        }
-
         for (uint64_t t = t_first; t < t_end; t += t_step) {
-            C w[NR];
-            const bool more = PF && t + t_step < t_end;
-            if constexpr (!PF) {
-                load(v, t);
-                if (t == t_first)
-                    touch_records(ops, n_ops, tid);
-                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), as above
-            } else if (more)
-                load(w, t + t_step);
+            load(v, t);
+            if (t == t_first)
+                touch_records(ops, n_ops, tid);
+            // wait for the tile here (vmcnt(0); expcnt and lgkmcnt left at their
+            // maxima), so that the operations wait for no global access
+            __builtin_amdgcn_s_waitcnt(0x0F70);
             const uint64_t base = tile_base(a, t);
 
             SlotOffs so = offs_plain();
@@ -976,13 +935,6 @@ template <typename R, int LOG_NT, int LOG_R, bool HALF = true, bool STREAM = tru
             if constexpr (ZB)
                 reduce_bits(zt, zu, direct ? fl : 0u, zparts + t, zstride, reinterpret_cast<double *>(lds));
             lds_sync();  // the next tile reuses the LDS buffer
-            if constexpr (PF) {
-                if (more) {
-#pragma unroll
-                    for (int j = 0; j < NR; ++j)
-                        v[j] = w[j];
-                }
-            }
         }
     }
 
@@ -1073,8 +1025,8 @@ __global__ __launch_bounds__(1 << LOG_NT) void k_tile(TileArgs a)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const uint64_t t = (uint64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    TileKernel<R, LOG_NT, LOG_R, true, STREAM>::template run_range<false, true, false, EXT>(a, lds_raw, t, t + 1, 1,
-                                                                                        {nullptr, 0});
+    TileKernel<R, LOG_NT, LOG_R, STREAM>::template run_range<true, false, EXT>(a, lds_raw, t, t + 1, 1,
+                                                                                    {nullptr, 0});
 }
 
 // The same pass with the ZB read-out of every tile into zparts.
@@ -1084,7 +1036,7 @@ __global__ __launch_bounds__(1 << LOG_NT) void k_tile_z(TileArgs a, double *zpar
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const uint64_t t = (uint64_t)blockIdx.y * gridDim.x + blockIdx.x;
     // value v of tile t at zparts[v * (tiles of the launch) + t]
-    TileKernel<R, LOG_NT, LOG_R, true, STREAM>::template run_range<false, true, true>(
+    TileKernel<R, LOG_NT, LOG_R, STREAM>::template run_range<true, true>(
         a, lds_raw, t, t + 1, 1, {nullptr, 0}, zparts, (uint64_t)gridDim.x * gridDim.y);
 }
 
