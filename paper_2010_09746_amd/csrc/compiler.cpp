@@ -1158,6 +1158,12 @@ int schedule_segment(const std::vector<LGate> &lg, const qs_gate *g, const std::
 // amplitudes plus one small factor per lane and spoke, where each OP_DIAG
 // multiplies half or more of the amplitudes it selects from.  A phase on a
 // register slot above 3 cannot be a spoke (the record holds four) and ends a run.
+//
+// The lanes' factors are products of up to 4 * 255 spokes, formed also where
+// the amplitudes are 0: with factors far from modulus 1 (gates need not be
+// unitary) they leave the range of the type although the amplitudes they meet
+// do not, and 0 times infinity is no longer 0.  So d must have a squared
+// modulus within 1/16 of 1, which keeps every product within 2^-48 and 2^45.
 struct DiagBits {
     bool ok = false;
     int bit[2] = {0, 0};  // control, target: slot s as s, thread tile bit b as 16 + b, position p as 64 + p
@@ -1167,6 +1173,9 @@ DiagBits diag_bits(const TileOp &o)
 {
     DiagBits d;
     if (o.kind != OP_DIAG || o.m[0] != 1.0 || o.m[1] != 0.0)
+        return d;
+    const double m2 = o.m[2] * o.m[2] + o.m[3] * o.m[3];
+    if (!(m2 >= 1.0 - 0.0625 && m2 <= 1.0 + 0.0625))
         return d;
     if (__builtin_popcount(o.rmask) + __builtin_popcount(o.lmask) + __builtin_popcountll(o.hmask) != 1)
         return d;
