@@ -66,7 +66,13 @@ __global__ __launch_bounds__(ZT) void k_zsum(const Cplx<R> *__restrict__ s, int 
     const int it_bits = L - VB > ZT_BITS ? L - VB - ZT_BITS : 0;
     const uint32_t iters = 1u << it_bits;
     const uint64_t base = (uint64_t)blockIdx.x << L;
-    const Vec *src = reinterpret_cast<const Vec *>(s + base);
+    // a wide load at the alignment of one amplitude (a copy, not a cast to the
+    // vector type): a server's complex64 request may begin at any of them
+    auto load = [&](uint64_t i) {
+        Vec x;
+        __builtin_memcpy(&x, s + base + (i << VB), sizeof x);
+        return x;
+    };
     double tot = 0.0, vec = 0.0, acc[IT];
 #pragma unroll
     for (int b = 0; b < IT; ++b)
@@ -76,7 +82,7 @@ __global__ __launch_bounds__(ZT) void k_zsum(const Cplx<R> *__restrict__ s, int 
             Vec v[U];
 #pragma unroll
             for (uint32_t u = 0; u < U; ++u)
-                v[u] = it + u < iters ? src[((uint64_t)(it + u) << ZT_BITS) + tid] : Vec(R(0));
+                v[u] = it + u < iters ? load(((uint64_t)(it + u) << ZT_BITS) + tid) : Vec(R(0));
             double p[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
