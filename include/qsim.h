@@ -368,7 +368,10 @@ qs_status qs_run_program_noalloc(qs_state *s, const qs_program *p);
 /* Amplitudes at count logical indices (host array) into out (host, 2*count
  * doubles, interleaved re, im). */
 qs_status qs_read_amplitudes(qs_state *s, const uint64_t *logical_idx, int64_t count, double *out);
-/* All 2^n amplitudes in logical order into out (host, 2^(n+1) doubles). */
+/* All 2^n amplitudes in logical order into out (host, 2^(n+1) doubles).  Uses
+ * up to 16 MiB of device memory, kept with the state; without room for it, or
+ * with another device than the state's current, the host reorders a copy of
+ * the whole state instead. */
 qs_status qs_read_state(qs_state *s, double *out);
 /* <Z_q> = sum_i |a_i|^2 (1 - 2 i_q) for q = 0..n-1 into out (host, n doubles). */
 qs_status qs_expect_z(qs_state *s, double *out);

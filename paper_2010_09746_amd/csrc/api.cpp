@@ -1106,6 +1106,21 @@ qs_status qs_read_amplitudes(qs_state *s, const uint64_t *idx, int64_t count, do
     });
 }
 
+// The whole state copied out, then put in order and FP64 by the host.
+static void read_state_on_host(qs_state *s, double *out)
+{
+    std::vector<unsigned char> raw(s->bytes);
+    hipchk(hipMemcpyAsync(raw.data(), s->buf, s->bytes, hipMemcpyDeviceToHost, s->stream), "hipMemcpyAsync");
+    hipchk(hipStreamSynchronize(s->stream), "hipStreamSynchronize");
+    const float *f = reinterpret_cast<const float *>(raw.data());
+    const double *d = reinterpret_cast<const double *>(raw.data());
+    for (uint64_t i = 0; i < (1ull << s->n); ++i) {
+        const uint64_t j = phys_index(i, s->sigma);
+        for (int c = 0; c < 2; ++c)
+            out[2 * i + c] = s->dt == QS_C64 ? (double)f[2 * j + c] : d[2 * j + c];
+    }
+}
+
 qs_status qs_read_state(qs_state *s, double *out)
 {
     return guard([&] {
@@ -1120,19 +1135,26 @@ qs_status qs_read_state(qs_state *s, double *out)
             hipchk(hipStreamSynchronize(s->stream), "hipStreamSynchronize");
             return;
         }
-        // put in logical order and FP64 on the device, up to 2^20 amplitudes
-        // (16 MiB of the state's read-out workspace) at a time
-        // (less when the device has no room for that)
-        uint64_t chunk = std::min<uint64_t>(N, 1ull << 20);
-        for (;;) {
+        // Put in logical order and FP64 on the device, up to 2^20 amplitudes
+        // (16 MiB of the state's read-out workspace) at a time, fewer where
+        // the device has less room.  Without room for 2^10, or with another
+        // device than the state's current, the host does it, as the copy
+        // alone needs neither.
+        int cur = -1;
+        hipchk(hipGetDevice(&cur), "hipGetDevice");
+        uint64_t chunk = cur == s->dev ? std::min<uint64_t>(N, 1ull << 20) : 0;
+        while (chunk)
             try {
                 ensure_work(s, 2 * chunk);
                 break;
-            } catch (const Error &) {
-                if (chunk <= 1024)
+            } catch (const Error &e) {
+                if (e.code != QS_ERR_OOM)
                     throw;
-                chunk >>= 2;
+                chunk = chunk > 1024 ? chunk >> 2 : 0;
             }
+        if (chunk == 0) {
+            read_state_on_host(s, out);
+            return;
         }
         for (uint64_t i = 0; i < N; i += chunk) {
             launch_logical(s->buf, s->dt, s->n, s->sigma, i, chunk, s->d_work, s->stream);
