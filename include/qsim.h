@@ -505,7 +505,10 @@ qs_status qs_server_fits(const qs_server *s, int n, int *fits);
  * state_buf: caller-owned device buffer of 2^n amplitudes (not freed by the
  * server; it must stay valid until qs_server_release).  samples: count
  * logical basis indices (host) whose amplitudes are returned.  Fails with
- * QS_ERR_BUDGET when the budget or the slots are exhausted. */
+ * QS_ERR_BUDGET when the budget or the slots are exhausted.  A program of up
+ * to 21 qubits compiled without reg_bits has a tile shape of its own: its
+ * first admission compiles it once more for the server's, which stays with
+ * the program (compile with the server's reg_bits to avoid that). */
 qs_status qs_server_admit(qs_server *s, const qs_program *p, void *state_buf, size_t buf_bytes,
                           const uint64_t *samples, int count, int64_t *request_id);
 /* Enqueue one step; *n_running receives the requests advanced.  Up to two

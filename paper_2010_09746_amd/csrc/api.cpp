@@ -489,13 +489,19 @@ void run_program_with_ops(qs_state *s, const Program &p, const TileOp *d_ops)
     s->sigma = p.sigma_final;
 }
 
-const Program &usual_shape(const Program &p, Program &tmp)
+const Program &usual_shape(const qs_program &pp)
 {
+    const Program &p = pp.p;
     if (!p.small_shape)
         return p;
-    compile_program(p.src.data(), (int64_t)p.src.size(), p.n, p.dt, p.sigma0.data(), p.opts, tmp, {},
-                    p.costed ? &p.costs : nullptr);
-    return tmp;
+    std::lock_guard<std::mutex> lk(pp.usual_mu);
+    if (!pp.usual) {
+        auto u = std::make_unique<Program>();
+        compile_program(p.src.data(), (int64_t)p.src.size(), p.n, p.dt, p.sigma0.data(), p.opts, *u, {},
+                        p.costed ? &p.costs : nullptr);
+        pp.usual = std::move(u);
+    }
+    return *pp.usual;
 }
 
 void *state_stream(const qs_state *s) { return s->stream; }

@@ -5,6 +5,8 @@
 
 #include <cstdint>
 #include <functional>
+#include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -215,6 +217,10 @@ void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int
 // handle behind qs_program
 struct qs_program {
     qsim::Program p;
+    // p compiled with the usual tile shape, made once when first asked for
+    // (usual_shape; a program may be used by several threads)
+    mutable std::mutex usual_mu;
+    mutable std::unique_ptr<qsim::Program> usual;
 };
 
 namespace qsim {
@@ -227,9 +233,9 @@ void tile_args_from_launch(const Launch &L, TileArgs &a);
 void tile_args_identity(int k, int log_nt, int log_r, TileArgs &a);
 void tile_args_for_positions(const std::vector<int> &pos, int log_nt, int log_r, TileArgs &a);
 
-// p itself, or compiled again into tmp with the usual tile shape when p has
-// that of a small state
-const Program &usual_shape(const Program &p, Program &tmp);
+// pp's program, or that program compiled with the usual tile shape when it has
+// the one of a small state (compiled on the first call and kept with pp)
+const Program &usual_shape(const qs_program &pp);
 
 // choose register bits / threads for a tile of k bits
 // Tile shape: 2^log_r amplitudes per thread (reg_bits_opt, or pass_reg_bits

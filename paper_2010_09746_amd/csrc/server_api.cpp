@@ -308,26 +308,35 @@ qs_status qs_server_admit(qs_server *s, const qs_program *pp, void *state_buf, s
     return guard([&] {
         if (!s || !pp || !state_buf || !request_id || count < 0 || count > s->max_samples || (count && !samples))
             fail(QS_ERR_ARG, "bad arguments");
-        // the shared launch has one tile shape, the usual one
-        Program tmp;
-        const Program &p = usual_shape(pp->p, tmp);
-        const int n = p.n;
+        const Program &asked = pp->p;
+        const int n = asked.n;
         const size_t eb = s->dt == QS_C64 ? 8 : 16;
         const size_t bytes = eb << n;
-        if (p.dt != s->dt)
+        if (asked.dt != s->dt)
             fail(QS_ERR_ARG, "program compiled for another amplitude type");
         if (n < s->K || n > MAX_QUBITS)
             fail(QS_ERR_ARG, "request needs k_tile <= n <= 34");
         if (buf_bytes < bytes)
             fail(QS_ERR_ARG, "state buffer smaller than 2^n amplitudes");
         for (int q = 0; q < n; ++q)
-            if (p.sigma0[q] != q)
+            if (asked.sigma0[q] != q)
                 fail(QS_ERR_ARG, "program must start from the identity placement");
         for (int i = 0; i < count; ++i)
             if (samples[i] >= (1ull << n))
                 fail(QS_ERR_ARG, "sample index out of range");
         if (s->resident + bytes > s->budget || s->free_slots.empty())
             fail(QS_ERR_BUDGET, "request does not fit the memory budget or the slots");
+        // The shared launch has one tile shape, the usual one: a program with
+        // that of a small state is compiled for it, once all that can be
+        // refused without that has been.
+        int log_r = 0, log_nt = 0;
+        for (const Launch &L : asked.launches) {
+            if (L.type == L_TILE)
+                tile_shape(L.k, asked.dt, asked.opts.reg_bits, &log_r, &log_nt);
+            if (L.type != L_TILE || L.k != s->K || log_r != s->log_r)
+                fail(QS_ERR_ARG, "program not compiled with this server's tile options (relabel, k_tile, reg_bits)");
+        }
+        const Program &p = usual_shape(*pp);
         SReq r;
         r.id = s->next_id;
         r.n = n;
@@ -335,11 +344,8 @@ qs_status qs_server_admit(qs_server *s, const qs_program *pp, void *state_buf, s
         r.bytes = bytes;
         r.ops = p.ops;
         std::vector<const Launch *> tl;
-        for (const Launch &L : p.launches) {
-            if (L.type != L_TILE || L.k != s->K || L.log_r != s->log_r)
-                fail(QS_ERR_ARG, "program not compiled with this server's tile options (relabel, k_tile, reg_bits)");
+        for (const Launch &L : p.launches)
             tl.push_back(&L);
-        }
         r.np = std::max<size_t>(1, tl.size());
         // arena space: ops, samples, read-out
         r.ops_len = std::max<size_t>(1, r.ops.size()) * sizeof(TileOp);
