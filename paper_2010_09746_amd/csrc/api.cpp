@@ -698,13 +698,9 @@ qs_status compile_entry(const qs_gate *gates, int64_t n_gates, int n, qs_dtype d
             check_costs(*costs);
         auto *p = new qs_program();
         try {
-            compile_program(gates, n_gates, n, dt, sigma0, o, p->p, {}, costs, true, true);
             // a small state's shape needs more records: where they pass the
             // limit of qs_run_program_noalloc the usual shape stays
-            if (p->p.small_shape && p->p.ops.size() > (size_t)QS_NOALLOC_MAX_OPS) {
-                p->p = Program();
-                compile_program(gates, n_gates, n, dt, sigma0, o, p->p, {}, costs);
-            }
+            compile_program(gates, n_gates, n, dt, sigma0, o, p->p, {}, costs, true, QS_NOALLOC_MAX_OPS);
             if (p->p.small_shape) {
                 p->p.src.assign(gates, gates + n_gates);
                 p->p.costed = costs != nullptr;
@@ -1020,7 +1016,7 @@ qs_status run_circuit_entry(qs_state *s, const qs_gate *gates, int64_t n_gates, 
         };
         if (o.form == QS_FORM_PASS) {
             try {
-                compile_program(gates, n_gates, s->n, s->dt, s->sigma.data(), o, p, progress, costs, true, true);
+                compile_program(gates, n_gates, s->n, s->dt, s->sigma.data(), o, p, progress, costs, true, ALL_OPS);
             } catch (...) {
                 // launches already enqueued read the op tables: let them
                 // finish before the error is reported (the state then holds a

@@ -1681,7 +1681,7 @@ void tile_args_identity(int k, int log_nt, int log_r, TileArgs &a)
 
 void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int *sigma0_in,
                      const qs_run_opts &o, Program &p, const std::function<void(Program &)> &progress,
-                     const qs_pass_costs *costs, bool fans, bool small_shapes)
+                     const qs_pass_costs *costs, bool fans, size_t small_ops)
 {
     auto t0 = std::chrono::steady_clock::now();
     if (n < 1 || n > MAX_COMPILE_QUBITS)
@@ -1778,18 +1778,28 @@ void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int
         int log_r = 0, log_nt = 0;
         if (tiled) {
             tile_shape(k, dt, o.reg_bits, &log_r, &log_nt);
-            if (small_shapes && o.reg_bits <= 0) {
+            if (small_ops && o.reg_bits <= 0) {
                 const int usual = log_r;
                 tile_shape(k, dt, small_state_reg_bits(n, k, dt), &log_r, &log_nt);
                 p.small_shape = log_r != usual;
             }
         }
-        std::vector<int> spass = p.sigma0;
-        size_t i = 0;
-        // reduced one-qubit updates only where tile passes run them
-        pf.on = tiled && (o.flags & QS_OPT_FULL_MATRICES) == 0;
-        if (pf.on)
-            pf.init(g, gi, ng, n, dt == QS_C128 || (o.flags & QS_OPT_X_FACTORS) != 0);
+        std::vector<int> spass;
+        size_t i;
+        // what the lowering starts from
+        auto begin = [&] {
+            p.launches.clear();
+            p.ops.clear();
+            p.stats.n_plain = p.stats.n_move_passes = p.stats.n_tile_passes = p.stats.n_remaps = 0;
+            sphys = spass = p.sigma0;
+            i = 0;
+            // reduced one-qubit updates only where tile passes run them
+            pf = PhaseFrame();
+            pf.on = tiled && (o.flags & QS_OPT_FULL_MATRICES) == 0;
+            if (pf.on)
+                pf.init(g, gi, ng, n, dt == QS_C128 || (o.flags & QS_OPT_X_FACTORS) != 0);
+        };
+        begin();
         const int lane_bits = (o.flags & QS_OPT_LANE_GATES_WIDE) ? 4 : (o.flags & QS_OPT_LANE_GATES) ? 2 : 0;
         const bool lane_eager = (o.flags & QS_OPT_LANE_EAGER) != 0;
         // Lower the instructions from i on.  A run of ApplyGate instructions is
@@ -1871,6 +1881,13 @@ void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int
                     ++p.stats.n_tile_passes;
                 }
                 i = j;
+                if (p.small_shape && p.ops.size() > small_ops) {
+                    // too many records: the usual shape, which needs fewer,
+                    // from the first instruction on (the pass's choices stay)
+                    p.small_shape = false;
+                    tile_shape(k, dt, o.reg_bits, &log_r, &log_nt);
+                    begin();
+                }
             }
         };
         // the pass and the lowering advance together, so a caller can start

@@ -205,12 +205,15 @@ struct Program {
 // iteration, once the launches of every completed segment are in p.launches
 // (and their operations in p.ops); launches already there never change.
 // Without fans, controlled phases stay one operation each (for the batching
-// form's kernel, which has no code for OP_FAN).  With small_shapes and no
-// reg_bits asked for, small states get the register bits of
-// small_state_reg_bits (p.small_shape: they differ from the usual ones).
+// form's kernel, which has no code for OP_FAN).  Where no reg_bits are asked
+// for, small states get the register bits of small_state_reg_bits
+// (p.small_shape: they differ from the usual ones) if their program then holds
+// at most small_ops records; with 0 no state does.  (A program that has been
+// given to progress is past changing: small_ops is ALL_OPS or 0 there.)
+constexpr size_t ALL_OPS = SIZE_MAX;
 void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int *sigma0,
                      const qs_run_opts &o, Program &p, const std::function<void(Program &)> &progress = {},
-                     const qs_pass_costs *costs = nullptr, bool fans = true, bool small_shapes = false);
+                     const qs_pass_costs *costs = nullptr, bool fans = true, size_t small_ops = 0);
 
 }  // namespace qsim
 
