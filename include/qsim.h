@@ -252,6 +252,12 @@ typedef struct {
  * entries give QS_ERR_ARG.  Otherwise as qs_compile. */
 qs_status qs_compile_costed(const qs_gate *gates, int64_t n_gates, int n, qs_dtype dt, const int *sigma0,
                             const qs_run_opts *opts, const qs_pass_costs *costs, qs_program **out);
+/* Register bits (log2 of the amplitudes per thread) of the tile passes of a
+ * program of n qubits compiled with k_tile and reg_bits (0: the library's
+ * choice, which up to 21 qubits is another one than above; a program that
+ * would then pass QS_NOALLOC_MAX_OPS has those of n = 0).  n = 0: those of a
+ * server with these options.  0 where the pass runs gate by gate. */
+qs_status qs_tile_reg_bits(int n, qs_dtype dt, int k_tile, int reg_bits, int *out);
 qs_status qs_program_destroy(qs_program *p);
 qs_status qs_program_get_stats(const qs_program *p, qs_program_stats *out);
 /* Work of a compiled program by class, for a cost model that prices each
@@ -508,7 +514,7 @@ qs_status qs_server_fits(const qs_server *s, int n, int *fits);
  * QS_ERR_BUDGET when the budget or the slots are exhausted.  A program of up
  * to 21 qubits compiled without reg_bits has a tile shape of its own: its
  * first admission compiles it once more for the server's, which stays with
- * the program (compile with the server's reg_bits to avoid that). */
+ * the program (compile with qs_tile_reg_bits(0, ...) to avoid that). */
 qs_status qs_server_admit(qs_server *s, const qs_program *p, void *state_buf, size_t buf_bytes,
                           const uint64_t *samples, int count, int64_t *request_id);
 /* Enqueue one step; *n_running receives the requests advanced.  Up to two

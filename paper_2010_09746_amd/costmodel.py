@@ -93,7 +93,9 @@ class CostModel:
 
     def __init__(self, dtype: str = "c128", n_cal: int = 27, perm_exec: str = "relabel", pinned: int = 3):
         self.dtype, self.n_cal, self.perm_exec, self.pinned = dtype, n_cal, perm_exec, pinned
-        self.tile_costs = {}   # (k, reg_bits) -> {class: ms at n_cal}
+        # (k, reg_bits) -> {class: ms at n_cal}; reg_bits 0 is the library's choice
+        # for large states (small ones have another: see _shape)
+        self.tile_costs = {}
         self.launch_costs = None
         self.fit_residual = {}
 
@@ -137,9 +139,10 @@ class CostModel:
     def calibrate_tile(self, st: Q.State, k: int, reg_bits: int = 0) -> dict:
         n = self.n_cal
         rows, times = [], []
-        for name, g in calibration_circuits(n, k, self._log_r(k, reg_bits)).items():
+        log_r = self._log_r(k, reg_bits)  # by name: at a small n_cal the library's own choice is another one
+        for name, g in calibration_circuits(n, k, log_r).items():
             prog = Q.Program(g, n, self.dtype, form="pass", k_tile=k, max_swaps=1, pinned=self.pinned,
-                             perm_exec=self.perm_exec, reg_bits=reg_bits, **CAL_OPTS.get(name, {}))
+                             perm_exec=self.perm_exec, reg_bits=log_r, **CAL_OPTS.get(name, {}))
             c = prog.op_counts()
             times.append(_pass_ms(st, prog))
             rows.append([c[x] for x in TILE_CLASSES])
@@ -151,27 +154,32 @@ class CostModel:
         self.tile_costs[(k, reg_bits)] = dict(zip(TILE_CLASSES, (float(v) for v in cost)))
         return self.tile_costs[(k, reg_bits)]
 
-    def _log_r(self, k: int, reg_bits: int) -> int:
-        # the library's tile shape of a pass: 16 amplitudes per thread by
-        # default (8 for complex128 below 2^11-amplitude tiles), at most 1024
-        # threads and at least one wavefront
-        lr = reg_bits if reg_bits > 0 else ((4 if k >= 11 else 3) if self.dtype == "c128" else 4)
-        lr = max(min(lr, 5), k - 10)
-        return max(min(lr, k - 6), 1)
+    def _log_r(self, k: int, reg_bits: int, n: int = 0) -> int:
+        """Register bits of the tile passes of programs of n qubits (0: of large states)."""
+        return Q.qs_tile_reg_bits(n, self.dtype, k, reg_bits)
+
+    def _shape(self, n: int, k: int, reg_bits: int) -> tuple:
+        """Key of the tile costs that programs of n qubits with these options have."""
+        log_r = self._log_r(k, reg_bits, n)
+        return (k, reg_bits) if log_r == self._log_r(k, reg_bits) else (k, log_r)
 
     def calibrate(self, shapes) -> None:
+        shapes = [s for s in shapes if s not in self.tile_costs]
+        if self.launch_costs is not None and not shapes:
+            return
         st = Q.State(self.n_cal, self.dtype)
         if self.launch_costs is None:
             self.calibrate_launches(st)
         for k, rb in shapes:
-            if (k, rb) not in self.tile_costs:
-                self.calibrate_tile(st, k, rb)
+            self.calibrate_tile(st, k, rb)
         st.close()
 
     # -- prediction -----------------------------------------------------------
     def predict_counts(self, counts: dict, n: int, k: int, reg_bits: int) -> float:
         scale = 2.0 ** (n - self.n_cal)
-        tc = self.tile_costs[(k, reg_bits)]
+        shape = self._shape(n, k, reg_bits)
+        self.calibrate([shape])
+        tc = self.tile_costs[shape]
         ms = sum(counts[c] * tc[c] for c in TILE_CLASSES)
         # a pending phase applied on its own touches half the amplitudes of
         # a diagonal update (rare: the W that left it ended an earlier pass)
@@ -189,9 +197,10 @@ class CostModel:
         non-diagonal target: the mean of register- and lane-controlled
         exchanges; diagonal: a sign flip), moving the whole state (moved
         placements only) and each gate kind as a launch of its own."""
-        self.calibrate([(k, reg_bits)])
+        shape = self._shape(n, k, reg_bits)
+        self.calibrate([shape])
         scale = 2.0 ** (n - self.n_cal)
-        tc, lc = self.tile_costs[(k, reg_bits)], self.launch_costs
+        tc, lc = self.tile_costs[shape], self.launch_costs
         return dict(tile=scale * (tc["tile_pass"] + 4 * tc["remap"]),
                     **{"in": (scale * tc["shear"], scale * 0.5 * (tc["x_reg"] + tc["x_lane"]), scale * tc["neg"])},
                     move=scale * lc["move_fraction"] if perm_exec == "move" else 0.0,
@@ -224,7 +233,7 @@ class CostModel:
             if cp:
                 c["costed"] = True
             cands.append(c)
-        self.calibrate({(c["k_tile"], c["reg_bits"]) for c in cands})
+        self.calibrate({self._shape(n, c["k_tile"], c["reg_bits"]) for c in cands})
         table = []
         for c in cands:
             ms, counts = self.predict(gates, n, **c)

@@ -730,6 +730,21 @@ qs_status qs_compile_costed(const qs_gate *gates, int64_t n_gates, int n, qs_dty
     return compile_entry(gates, n_gates, n, dt, sigma0, opts, costs, out);
 }
 
+qs_status qs_tile_reg_bits(int n, qs_dtype dt, int k_tile, int reg_bits, int *out)
+{
+    return guard([&] {
+        need(out != nullptr, "out is NULL");
+        need(n >= 0 && n <= MAX_COMPILE_QUBITS, "n must be in [0, 63]");
+        need(dt == QS_C64 || dt == QS_C128, "unknown dtype");
+        need(k_tile >= 1, "k_tile must be >= 1");
+        const int k = n > 0 ? std::min(k_tile, n) : k_tile;
+        int log_r = 0, log_nt = 0;
+        if (tiled_pass(k, dt))
+            tile_shape(k, dt, n > 0 && reg_bits <= 0 ? small_state_reg_bits(n, k, dt) : reg_bits, &log_r, &log_nt);
+        *out = log_r;
+    });
+}
+
 qs_status qs_program_destroy(qs_program *p)
 {
     return guard([&] {

@@ -511,6 +511,11 @@ void tile_shape(int k, qs_dtype dt, int reg_bits_opt, int *log_r, int *log_nt)
     *log_nt = k - lr;
 }
 
+bool tiled_pass(int k, qs_dtype dt)
+{
+    return k >= MIN_TILE_BITS && (size_t(dt == QS_C64 ? 8 : 16) << k) <= MAX_TILE_BYTES;
+}
+
 namespace {
 
 // A gate lowered to tile-local form, before register slots are assigned.
@@ -1774,7 +1779,7 @@ void compile_program(const qs_gate *g, int64_t ng, int n, qs_dtype dt, const int
         // tile passes need 7 <= k and a tile that fits in one CU's LDS; a larger
         // local set (e.g. a pass planned for several devices) runs its
         // segments gate by gate
-        const bool tiled = k >= MIN_TILE_BITS && (size_t(dt == QS_C64 ? 8 : 16) << k) <= MAX_TILE_BYTES;
+        const bool tiled = tiled_pass(k, dt);
         int log_r = 0, log_nt = 0;
         if (tiled) {
             tile_shape(k, dt, o.reg_bits, &log_r, &log_nt);

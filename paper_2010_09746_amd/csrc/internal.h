@@ -248,6 +248,8 @@ void tile_shape(int k, qs_dtype dt, int reg_bits_opt, int *log_r, int *log_nt);
 int pass_reg_bits(int k, qs_dtype dt);
 // the same for one state of n qubits run by itself
 int small_state_reg_bits(int n, int k, qs_dtype dt);
+// whether a pass over k local qubits runs as tile passes
+bool tiled_pass(int k, qs_dtype dt);
 
 // ---------------------------------------------------------------------------
 // state access for entry points defined outside api.cpp

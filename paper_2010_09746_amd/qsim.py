@@ -48,6 +48,7 @@ EXPORTS = [
     "qs_server_create", "qs_server_destroy", "qs_server_fits", "qs_server_admit", "qs_server_step_launch",
     "qs_server_step_wait", "qs_server_result", "qs_server_release", "qs_server_set_solo_tiles",
     "qs_run_program_noalloc", "qs_compile_costed", "qs_run_circuit_costed", "qs_run_circuit_expect_z",
+    "qs_tile_reg_bits",
 ]
 
 
@@ -142,6 +143,7 @@ def load() -> ctypes.CDLL:
                              ctypes.POINTER(qs_run_opts), ctypes.POINTER(_vp)]
     L.qs_compile_costed.argtypes = [_vp, ctypes.c_int64, ctypes.c_int, ctypes.c_int, _ip,
                                     ctypes.POINTER(qs_run_opts), ctypes.POINTER(qs_pass_costs), ctypes.POINTER(_vp)]
+    L.qs_tile_reg_bits.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, _ip]
     L.qs_program_destroy.argtypes = [_vp]
     L.qs_program_get_stats.argtypes = [_vp, ctypes.POINTER(qs_program_stats)]
     L.qs_program_op_counts.argtypes = [_vp, ctypes.POINTER(ctypes.c_double), ctypes.c_int]
@@ -320,6 +322,12 @@ def qs_compile_costed(gates, n: int, dtype, sigma0=None, opts: qs_run_opts | Non
                                   ctypes.byref(opts) if opts is not None else None,
                                   ctypes.byref(costs) if costs is not None else None, ctypes.byref(h)))
     return h.value
+
+
+def qs_tile_reg_bits(n: int, dtype, k_tile: int, reg_bits: int = 0) -> int:
+    out = ctypes.c_int()
+    _chk(load().qs_tile_reg_bits(n, _dtype_code(dtype), k_tile, reg_bits, ctypes.byref(out)))
+    return out.value
 
 
 def qs_program_destroy(h: int) -> None:

@@ -60,12 +60,10 @@ class Server:
             pass
 
     def compile(self, gates, n) -> Q.Program:
-        # the server's tile shape by name (the library's usual one when none is
-        # asked for): a small state compiled for a run of its own gets another
-        # one, and admission would compile it again
-        usual = 4 if self.eb == 8 or self.k_tile >= 11 else 3
+        # the server's tile shape by name: a small state compiled for a run of its
+        # own gets another one, and admission would compile it again
         return Q.Program(gates, n, self.dtype, form="pass", k_tile=self.k_tile, max_swaps=self.max_swaps,
-                         pinned=self.pinned, perm_exec="relabel", reg_bits=self.reg_bits or usual)
+                         pinned=self.pinned, perm_exec="relabel", reg_bits=Q.qs_tile_reg_bits(0, self.dtype, self.k_tile, self.reg_bits))
 
     def serve(self, requests, realtime=True, log=None):
         """requests: dicts with id, arrival (s), n, gates, samples.  Returns
