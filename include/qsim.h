@@ -280,6 +280,9 @@ qs_status qs_program_get_stats(const qs_program *p, qs_program_stats *out);
  *   QS_OPC_LANE        one-qubit gates through lane exchanges (see flags)
  *   QS_OPC_REMAP_WAVE  re-layouts that keep the tile bits on the wavefront
  *                      bits of the thread id (no barrier; also in QS_OPC_REMAP)
+ *   QS_OPC_FAN         groups of controlled phases that share a bit (weighted
+ *                      by it) and run as one multiplication by a factor per
+ *                      thread; QS_OPC_FAN_PHASE their phases (also in QS_OPC_DIAG)
  * Writes min(cap, QS_OPC_COUNT) entries. */
 enum {
     QS_OPC_TILE_PASS = 0,
@@ -302,7 +305,9 @@ enum {
     QS_OPC_LSWAP = 17,     /* register slot bit <-> lane bit exchange (no LDS) */
     QS_OPC_LANE = 18,      /* one-qubit 2x2 on a lane bit through lane exchanges */
     QS_OPC_REMAP_WAVE = 19, /* re-layouts (counted in QS_OPC_REMAP too) local to each wavefront: no barrier */
-    QS_OPC_COUNT = 20
+    QS_OPC_FAN = 20,       /* groups of controlled phases that share a bit, run together */
+    QS_OPC_FAN_PHASE = 21, /* the part of QS_OPC_DIAG that runs in such groups */
+    QS_OPC_COUNT = 22
 };
 qs_status qs_program_op_counts(const qs_program *p, double *out, int cap);
 

@@ -40,7 +40,8 @@ from . import qsim as Q
 
 from workloads import KIND_CU, KIND_CX, KIND_CZ, KIND_U, haar_u2, make_gates, phase
 
-TILE_CLASSES = ["tile_pass", "u", "shear", "u_ctrl", "x_reg", "x_lane", "neg", "diag", "remap", "dispatch"]
+TILE_CLASSES = ["tile_pass", "u", "shear", "u_ctrl", "x_reg", "x_lane", "neg", "diag", "remap", "dispatch", "fan",
+                "fan_phase"]
 # compile options of calibration circuits that need them: "u" measures whole
 # 2x2 updates, so its circuit keeps every matrix whole
 CAL_OPTS = {"u": dict(full_matrices=True)}
@@ -70,6 +71,8 @@ def calibration_circuits(n: int, k: int, log_r: int, seed: int = 20100946 + 9) -
     N = 160
     st = next(s for s in (7, 5, 3, 11, 13) if math.gcd(s, k) == 1 and s % k)
     U = lambda q: (KIND_U, q, -1, haar_u2(rng))
+    rim = list(range(max(2, R), k))
+    fans = lambda m: [(KIND_CU, rim[i % len(rim)], i // m % 2, phase(0.1 + 0.01 * i)) for i in range(N)]
     c = {
         "base": [U(0)],
         "u": [U(q % R) for q in range(N + 1)],
@@ -83,9 +86,18 @@ def calibration_circuits(n: int, k: int, log_r: int, seed: int = 20100946 + 9) -
         "dispatch": [U(0)] + [(KIND_CX, n - 1, q % R, None) for q in range(N)],
         # a dependency chain over all tile qubits: each gate's target is the
         # previous gate's, so most steps need a new register layout
+        # controlled phases around two qubits in turn, with three or all of the
+        # tile's qubits beyond the register slots at a time
+        "fan": [U(q) for q in range(R)] + fans(3),
+        "fan_phase": [U(q) for q in range(R)] + fans(len(rim)),
         "remap": [g for i in range(N // 2) for g in (U((st * i) % k), (KIND_CX, (st * i) % k, (st * i + st) % k, None))],
     }
     return {name: make_gates(g) for name, g in c.items() if g is not None}
+
+
+def tile_work(counts: dict) -> list:
+    """Work counts of the in-pass classes, each phase in one of them: "diag" without those that run in fans."""
+    return [counts[c] - (counts["fan_phase"] if c == "diag" else 0.0) for c in TILE_CLASSES]
 
 
 class CostModel:
@@ -145,7 +157,7 @@ class CostModel:
                              perm_exec=self.perm_exec, reg_bits=log_r, **CAL_OPTS.get(name, {}))
             c = prog.op_counts()
             times.append(_pass_ms(st, prog))
-            rows.append([c[x] for x in TILE_CLASSES])
+            rows.append(tile_work(c))
             prog.close()
         A, t = np.array(rows), np.array(times)
         cost, *_ = np.linalg.lstsq(A, t, rcond=None)
@@ -180,7 +192,7 @@ class CostModel:
         shape = self._shape(n, k, reg_bits)
         self.calibrate([shape])
         tc = self.tile_costs[shape]
-        ms = sum(counts[c] * tc[c] for c in TILE_CLASSES)
+        ms = sum(w * tc[c] for c, w in zip(TILE_CLASSES, tile_work(counts)))
         # a pending phase applied on its own touches half the amplitudes of
         # a diagonal update (rare: the W that left it ended an earlier pass)
         ms += counts["phase"] * 0.5 * tc["diag"]

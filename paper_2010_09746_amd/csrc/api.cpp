@@ -800,12 +800,15 @@ qs_status qs_program_op_counts(const qs_program *p, double *out, int cap)
                         continue;
                     }
                     if (o.kind == OP_FAN || o.kind == OP_SPOKES) {
+                        if (o.kind == OP_FAN)
+                            c[QS_OPC_FAN] += o.slot == -2 ? 0.5 : 1.0;
                         // each spoke is one controlled phase, counted as OP_DIAG
                         for (int s = 0; s < 4; ++s) {
                             const bool spoke = o.kind == OP_FAN ? ((o.rmask >> s) & 1u) != 0
                                                                 : ((o.rmask >> (8 * s)) & 255u) != SPOKE_NONE;
                             const double w = (o.aux >> (FAN_HCTRL + s)) & 1u ? 0.5 : 1.0;
                             c[QS_OPC_DIAG] += spoke ? w : 0.0;
+                            c[QS_OPC_FAN_PHASE] += spoke ? w : 0.0;
                             c[QS_OPC_DISPATCH] += spoke ? 1.0 - w : 0.0;
                         }
                         continue;
