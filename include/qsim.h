@@ -409,7 +409,9 @@ qs_status qs_synchronize(qs_state *s);
  *              choice).  Batch: ignored (256 threads per tile,
  *              2^(k - 8) amplitudes each)
  *   max_fuse   gates per tile pass bound (0 = none)
- *   wg_per_cu  workgroups per compute unit of the persistent launch (0 = 4)
+ *   wg_per_cu  workgroups per compute unit of the persistent launch (0 = 4); a
+ *              batch takes fewer where its circuits have too few tiles at a
+ *              time to keep that many at work
  *   chunk      largest number of tiles per work item (0 = 1); items are smaller
  *              where larger ones would leave compute units idle
  *   use_graph  batch: 1 = capture the run once in a HIP graph and replay it

@@ -34,6 +34,7 @@ struct BatchPlan {
     std::vector<PlanPass> passes;
     std::vector<std::vector<int>> circ_passes;   // pass indices of each circuit, in order
     std::vector<QueueItem> items;
+    size_t widest = 0;                           // items of the level that has most
 };
 
 constexpr int BATCH_MIN_TILE = QUEUE_LOG_NT + QUEUE_MIN_SHAPE;  // 9
@@ -143,6 +144,7 @@ void plan_batch(int count, const int *n, const qs_gate *const *gates, const int6
             if (lvl < bp.circ_passes[c].size())
                 tiles += bp.passes[bp.circ_passes[c][lvl]].tiles;
         const uint32_t chunk = tiles_per_item(tiles, o.chunk);
+        const size_t level_begin = bp.items.size();
         for (int c : order) {
             if (lvl >= bp.circ_passes[c].size())
                 continue;
@@ -160,6 +162,7 @@ void plan_batch(int count, const int *n, const qs_gate *const *gates, const int6
                 bp.items.push_back(it);
             }
         }
+        bp.widest = std::max(bp.widest, bp.items.size() - level_begin);
     }
 }
 
@@ -425,7 +428,7 @@ qs_status qs_batch_create(int count, const int *n_qubits, const qs_gate *const *
             int dev = 0, cus = 0;
             hipchk(hipGetDevice(&dev), "hipGetDevice");
             hipchk(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "hipDeviceGetAttribute");
-            b->grid = std::max(1, cus * (o.wg_per_cu > 0 ? o.wg_per_cu : 4));
+            b->grid = std::max(1, cus) * queue_workgroups_per_cu(bp.widest, cus, o.wg_per_cu > 0 ? o.wg_per_cu : 4);
             b->stats.state_bytes = (double)(b->total * eb);
         } catch (...) {
             free_batch(b);

@@ -84,16 +84,36 @@ struct QueueArgs {
 // is resident.  With fewer items whole compute units idle while others work
 // through several tiles, and the next pass waits for the last of them; with
 // more than a few rounds of items a larger item costs fewer tickets and cache
-// write-backs.  One run of a batch (complex64, tiles of 2^12) by tiles per
-// item 1, 2, 4, 8: 64 circuits of 10-20 qubits (about 3000 tiles per level)
-// 2.08, 2.07, 6.87, 9.41 ms; 30 circuits of 10-21 qubits (2600) 4.09, 3.09,
-// 4.14, 16.9 ms; 90 of 10-16 qubits (420) 3.83, 3.99, 5.76, 7.63 ms; 200 of
-// 10-22 qubits (31000) 39.5, 26.9, 22.8, 22.2 ms.
+// write-backs.  One run of a batch (k_tile 12, device time) with 1, 2, 4, 8
+// tiles in every item: complex64, 64 circuits of 10-20 qubits (2900 tiles per
+// level) 3.01, 2.71, 3.54, 5.87 ms; 20 of 12-21 qubits (990) 1.24, 1.63, 1.87,
+// 3.21 ms; 90 of 10-16 qubits (440) 0.65, 0.78, 1.37, 2.58 ms; 200 of 10-22
+// qubits (29000) 45.8, 30.9, 25.1, 23.6 ms; complex128, 64 of 10-20 qubits 3.51,
+// 2.91, 3.66, 5.54 ms; 100 of 10-21 qubits (8000) 8.34, 5.96, 4.93, 4.94 ms.
 inline uint32_t tiles_per_item(uint64_t tiles, int32_t chunk)
 {
     constexpr uint64_t ITEMS = 5 * 256;
     const uint64_t most = chunk > 1 ? (uint64_t)chunk : 1, fit = tiles / ITEMS;
     return (uint32_t)(fit < 1 ? 1 : fit < most ? fit : most);
+}
+
+// Workgroups per compute unit of a batch's persistent launch: the caller's
+// bound (options' wg_per_cu), but about two items of the widest level for each
+// workgroup, and one workgroup per compute unit at least.  A workgroup beyond
+// the items that can run takes one that must wait, so that compute units hold
+// waiting workgroups while others work on several items at once.  One run,
+// device time, chunk 1, four workgroups per compute unit against this rule, by
+// items in the widest level: 196 (16 circuits of 10-18 qubits, k_tile 12) 615,
+// 519 us complex64, 584, 520 us complex128; 768 (19 and 20 qubits, k_tile 11)
+// 2810, 1530 and 2422, 1690 us; 990 (20 of 12-21 qubits, k_tile 12) 2095, 1215
+// and 1874, 1215 us; with 1980 (the same, k_tile 11) four, three or two per
+// compute unit take 2250, 2060, 2300 us complex64, and from 2900 on four are
+// best (64 of 10-20 qubits, k_tile 12: 3000, 3250, 4000 us complex64).
+inline int queue_workgroups_per_cu(size_t widest, int cus, int wg_per_cu)
+{
+    const size_t most = wg_per_cu > 1 ? (size_t)wg_per_cu : 1, two = 2 * (size_t)(cus > 1 ? cus : 1);
+    const size_t fit = (widest + two - 1) / two;
+    return (int)(fit < 1 ? 1 : fit < most ? fit : most);
 }
 
 // A range of tiles of one pass: the unit of work of a level launch.

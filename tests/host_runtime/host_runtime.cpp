@@ -1,8 +1,8 @@
 // The HIP calls and kernel launchers that the library's host sources need, on
 // host memory, so that their allocation, admission and error paths run without
 // a GPU.  Device memory is a byte budget that the test sets; the launchers
-// that the tested paths reach work on the host (data movement and tile
-// passes leave the amplitudes alone), every other one fails.
+// that the tested paths reach work on the host (data movement, tile
+// passes and batches leave the amplitudes alone), every other one fails.
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -20,6 +20,7 @@ long mallocs = 0;
 std::map<void *, size_t> blocks;
 hipError_t malloc_error = hipSuccess;  // returned by every hipMalloc when set
 int device = 0;
+int queue_grid = 0;
 
 [[noreturn]] void not_here(const char *what) { fail(QS_ERR_UNSUPPORTED, std::string("no host version of ") + what); }
 
@@ -33,6 +34,7 @@ size_t host_used() { return used; }
 long host_mallocs() { return mallocs; }
 void host_set_malloc_error(int e) { malloc_error = (hipError_t)e; }
 void host_set_device(int d) { device = d; }
+int host_queue_grid() { return queue_grid; }  // workgroups of the last batch launch
 
 // ---- HIP
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -146,9 +148,9 @@ void launch_batch_reduce(const double *, const uint64_t *, const uint32_t *, int
 {
     not_here("a batch");
 }
-void launch_queue_reset(uint32_t *, uint64_t, hipStream_t) { not_here("a batch"); }
-void launch_batch_queue_f32(const QueueArgs &, int, hipStream_t) { not_here("a batch"); }
-void launch_batch_queue_f64(const QueueArgs &, int, hipStream_t) { not_here("a batch"); }
+void launch_queue_reset(uint32_t *, uint64_t, hipStream_t) {}
+void launch_batch_queue_f32(const QueueArgs &, int grid, hipStream_t) { queue_grid = grid; }
+void launch_batch_queue_f64(const QueueArgs &, int grid, hipStream_t) { queue_grid = grid; }
 void launch_zsum(const void *, qs_dtype, int, double *, double *, hipStream_t) { not_here("read-out sums"); }
 void launch_zfold(const double *, uint64_t, int, int, const ZFoldMap &, double *, double *, hipStream_t)
 {
