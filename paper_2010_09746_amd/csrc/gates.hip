@@ -369,9 +369,16 @@ template <typename R> static void involution_t(void *state, int n, const std::ve
         in[p] = in[pi[p]] = 1;
     for (int p = 0; p < n; ++p)
         J.K += in[p];
+    // Smaller tiles for small states, so that 2^10 of them are in flight: up to
+    // 2^20 amplitudes a launch is as long as one workgroup's chain of loads,
+    // LDS and stores.  Two moves, 16 qubits complex64: a random placement 51 us
+    // with tiles of 2^12, 19 with 2^8, the reversal 24, 13; 20 qubits: 58, 35
+    // and 26, 17; complex128, 17 qubits, a rotation 33, 21; 2^11 tiles are
+    // slower again (20 qubits complex64, the reversal 38).
+    const int most = std::min(INV_BITS<R>, std::max(2 * line_bits<R>(), n - 10));
     for (int p = 0; p < n; ++p) {
         const int need = pi[p] == p ? 1 : 2;
-        if (!in[p] && J.K + need <= INV_BITS<R>) {
+        if (!in[p] && J.K + need <= most) {
             in[p] = in[pi[p]] = 1;
             J.K += need;
         }
