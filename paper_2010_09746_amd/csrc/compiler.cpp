@@ -114,51 +114,71 @@ Dag build_dag(const qs_gate *g, const std::vector<GateInfo> &gi, int n, const st
     auto at = [&](int v) { return sel ? (*sel)[v] : v; };
     auto commute = [&](int a, int b) { return gates_commute(g[at(a)], gi[at(a)], g[at(b)], gi[at(b)]); };
     Dag d;
-    d.pred.resize(ng);
-    d.succ.resize(ng);
-    std::vector<std::vector<int>> uses(n);
-    // cut[q]: every gate on q before uses[q][cut[q]] is an ancestor of that
+    d.pred_at.assign(ng + 1, 0);
+    d.succ_at.assign(ng + 1, 0);
+    // the gates on qubit q so far: uses[use_at[q]] .. uses[use_end[q] - 1]
+    std::vector<int> use_at(n + 1, 0), use_end(n), uses;
+    for (int v = 0; v < ng; ++v) {
+        const GateInfo &iv = gi[at(v)];
+        ++use_at[iv.q0 + 1];
+        if (iv.nq == 2)
+            ++use_at[iv.q1 + 1];
+    }
+    for (int q = 0; q < n; ++q) {
+        use_at[q + 1] += use_at[q];
+        use_end[q] = use_at[q];
+    }
+    uses.resize(use_at[n]);
+    // cut[q]: every gate on q before uses[cut[q]] is an ancestor of that
     // gate, so a gate that depends on it needs no edge from them (the edges
     // left out are implied, readiness is unchanged)
-    std::vector<size_t> cut(n, 0);
+    std::vector<int> cut(use_at.begin(), use_at.begin() + n);
     std::vector<int> seen(ng, -1);
     for (int v = 0; v < ng; ++v) {
         const GateInfo &iv = gi[at(v)];
         const int qs[2] = {iv.q0, iv.q1};
         bool all_pred[2] = {true, true};
+        const size_t first = d.pred.size();
         for (int k = 0; k < iv.nq; ++k) {
-            const std::vector<int> &u = uses[qs[k]];
+            const int q = qs[k];
             // the cut gate commuting with v (an identical gate) implies nothing
-            size_t lo = cut[qs[k]];
-            if (lo < u.size() && commute(u[lo], v))
-                lo = 0;
-            for (size_t i = lo; i < u.size(); ++i) {
-                const int h = u[i];
+            int lo = cut[q];
+            if (lo < use_end[q] && commute(uses[lo], v))
+                lo = use_at[q];
+            for (int i = lo; i < use_end[q]; ++i) {
+                const int h = uses[i];
                 if (seen[h] == v) {
-                    all_pred[k] = all_pred[k] && !d.pred[v].empty() &&
-                                  std::find(d.pred[v].begin(), d.pred[v].end(), h) != d.pred[v].end();
+                    all_pred[k] = all_pred[k] && std::find(d.pred.begin() + first, d.pred.end(), h) != d.pred.end();
                     continue;
                 }
                 seen[h] = v;
                 if (!commute(h, v))
-                    d.pred[v].push_back(h);
+                    d.pred.push_back(h);
                 else
                     all_pred[k] = false;
             }
-            all_pred[k] = all_pred[k] && lo == cut[qs[k]];
+            all_pred[k] = all_pred[k] && lo == cut[q];
         }
-        std::sort(d.pred[v].begin(), d.pred[v].end());
-        for (int h : d.pred[v])
-            d.succ[h].push_back(v);
+        std::sort(d.pred.begin() + first, d.pred.end());
+        d.pred_at[v + 1] = d.pred.size();
         for (int k = 0; k < iv.nq; ++k) {
             const int q = qs[k];
             // v acts on q with a general matrix and depends on every gate on q
             // from the cut on: every earlier gate on q is now its ancestor
             if (act_on(iv, q) == ACT_G && all_pred[k])
-                cut[q] = uses[q].size();
-            uses[q].push_back(v);
+                cut[q] = use_end[q];
+            uses[use_end[q]++] = v;
         }
     }
+    for (int h : d.pred)
+        ++d.succ_at[h + 1];
+    for (int v = 0; v < ng; ++v)
+        d.succ_at[v + 1] += d.succ_at[v];
+    d.succ.resize(d.pred.size());
+    std::vector<size_t> next(d.succ_at.begin(), d.succ_at.end() - 1);
+    for (int v = 0; v < ng; ++v)
+        for (size_t i = d.pred_at[v]; i < d.pred_at[v + 1]; ++i)
+            d.succ[next[d.pred[i]]++] = v;
     return d;
 }
 
@@ -174,10 +194,10 @@ using MinHeap = std::priority_queue<int, std::vector<int>, std::greater<int>>;
 class PassState {
 public:
     PassState(const std::vector<GateInfo> &gi, const Dag &d, int n, int m)
-        : gi_(gi), d_(d), n_(n), m_(m), npend_(gi.size()), tmp_(gi.size(), -1), done_(gi.size(), 0)
+        : gi_(gi), d_(d), n_(n), m_(m), npend_(gi.size()), tmp_(gi.size(), -1), wait_next_(gi.size(), -1), done_(gi.size(), 0)
     {
         for (size_t v = 0; v < gi.size(); ++v) {
-            npend_[v] = (int)d.pred[v].size();
+            npend_[v] = d.n_pred((int)v);
             if (npend_[v] == 0)
                 frontier_.push_back((int)v);
         }
@@ -206,12 +226,10 @@ public:
     }
 
     // Number of not-scheduled gates that become schedulable under sigma;
-    // optionally collects the non-diagonal targets (qubits) of gates that are
-    // reached (all predecessors done or counted) but are not local, and the
-    // counted gates by cost class (gate_class).
+    // by cost class (gate_class) into classes too.
     // The closure does not depend on the order gates are visited in, so a
     // plain work list replaces the program-order heap of sweep().
-    int64_t closure(const int *sigma, std::vector<char> *reach_targets, int64_t *classes = nullptr)
+    int64_t closure(const int *sigma, int64_t *classes)
     {
         work_.assign(frontier_.begin(), frontier_.end());
         touched_.clear();
@@ -219,15 +237,11 @@ public:
         while (!work_.empty()) {
             const int v = work_.back();
             work_.pop_back();
-            if (!is_local(gi_[v], sigma, m_)) {
-                if (reach_targets)
-                    (*reach_targets)[gi_[v].target] = 1;
+            if (!is_local(gi_[v], sigma, m_))
                 continue;
-            }
             ++cnt;
-            if (classes)
-                ++classes[gate_class(gi_[v])];
-            for (int s : d_.succ[v]) {
+            ++classes[gate_class(gi_[v])];
+            for (int s : d_.succs(v)) {
                 if (tmp_[s] < 0) {
                     tmp_[s] = npend_[s];
                     touched_.push_back(s);
@@ -244,54 +258,34 @@ public:
     // closure() of every placement that exchanges local qubit l of sigma with
     // one of the qubits g (targets[g], not local), into counts[g].  The gates
     // that run with l moved out are followed once; for each g the closure goes
-    // on from the gates that wait for g and is then taken back.  (One closure per
-    // pair before: the pass's choices for 30 qubits, 40 layers, 9.6 -> 2.7 ms.)
-    void exchange_counts(const int *sigma, int l, const std::vector<char> &targets, std::vector<int64_t> &counts)
+    // on from the gates that wait for g and is then taken back.  (With one
+    // closure per pair the compile of 30 qubits, 40 layers took 10.2 instead of
+    // 4.7 ms.  The waiting gates are chained lists and the graph is held in flat
+    // arrays: with a vector for each, circuits of CNOTs on few qubits, which
+    // have few pairs to try, took longer than with the closures; 168 of them on
+    // 14 qubits, tiles of 10: 0.58 ms with closures, 0.65, now 0.42.)
+    // With l = -1 (no qubit moved out) it also finds the targets: the qubits
+    // that reached gates wait for.
+    void exchange_counts(const int *sigma, int l, std::vector<char> &targets, std::vector<int64_t> &counts)
     {
-        auto local = [&](int v) {
-            const int t = gi_[v].target;
-            return t < 0 || (sigma[t] < m_ && t != l);
-        };
-        waiting_.resize(n_);
-        for (auto &w : waiting_)
-            w.clear();
+        // the gates that wait for qubit q: a list from wait_[q] through wait_next_
+        wait_.assign(n_, -1);
         touched_.clear();
-        int64_t base = 0;
-        auto follow = [&](int g, std::vector<int> *undo) {
-            int64_t cnt = 0;
-            while (!work_.empty()) {
-                const int v = work_.back();
-                work_.pop_back();
-                if (!local(v) && gi_[v].target != g) {
-                    if (!undo)
-                        waiting_[gi_[v].target].push_back(v);
-                    continue;
-                }
-                ++cnt;
-                for (int s : d_.succ[v]) {
-                    if (tmp_[s] < 0) {
-                        tmp_[s] = npend_[s];
-                        touched_.push_back(s);
-                    }
-                    if (undo)
-                        undo->push_back(s);
-                    if (--tmp_[s] == 0)
-                        work_.push_back(s);
-                }
-            }
-            return cnt;
-        };
         work_.assign(frontier_.begin(), frontier_.end());
-        base = follow(-1, nullptr);
+        const int64_t base = follow(sigma, l, -1, false);
+        if (l < 0)
+            for (int g = 0; g < n_; ++g)
+                targets[g] = wait_[g] >= 0;
         for (int g = 0; g < n_; ++g) {
             if (!targets[g] || sigma[g] < m_)
                 continue;
             counts[g] = base;
-            if (waiting_[g].empty())
+            if (wait_[g] < 0)
                 continue;
             undo_.clear();
-            work_.assign(waiting_[g].begin(), waiting_[g].end());
-            counts[g] += follow(g, &undo_);
+            for (int v = wait_[g]; v >= 0; v = wait_next_[v])
+                work_.push_back(v);
+            counts[g] += follow(sigma, l, g, true);
             for (int s : undo_)
                 ++tmp_[s];
         }
@@ -319,11 +313,43 @@ public:
     }
 
 private:
+    // The closure from the gates in work_ on, with local qubit l moved out and
+    // qubit g moved in.  Gates that are reached and not local go to the lists of
+    // waiting gates, or, with undo, only what has been counted down is noted.
+    int64_t follow(const int *sigma, int l, int g, bool undo)
+    {
+        int64_t cnt = 0;
+        while (!work_.empty()) {
+            const int v = work_.back();
+            work_.pop_back();
+            const int t = gi_[v].target;
+            if (t >= 0 && t != g && (sigma[t] >= m_ || t == l)) {
+                if (!undo) {
+                    wait_next_[v] = wait_[t];
+                    wait_[t] = v;
+                }
+                continue;
+            }
+            ++cnt;
+            for (int s : d_.succs(v)) {
+                if (tmp_[s] < 0) {
+                    tmp_[s] = npend_[s];
+                    touched_.push_back(s);
+                }
+                if (undo)
+                    undo_.push_back(s);
+                if (--tmp_[s] == 0)
+                    work_.push_back(s);
+            }
+        }
+        return cnt;
+    }
+
     void mark_done(int v, MinHeap *h, std::vector<int> *newly = nullptr)
     {
         done_[v] = 1;
         --remaining_;
-        for (int s : d_.succ[v])
+        for (int s : d_.succs(v))
             if (--npend_[s] == 0) {
                 if (h)
                     h->push(s);
@@ -335,8 +361,7 @@ private:
     const std::vector<GateInfo> &gi_;
     const Dag &d_;
     int n_, m_;
-    std::vector<int> npend_, tmp_, touched_, work_, undo_;
-    std::vector<std::vector<int>> waiting_;
+    std::vector<int> npend_, tmp_, touched_, work_, undo_, wait_, wait_next_;
     std::vector<char> done_;
     std::vector<int> frontier_;
     int64_t remaining_;
@@ -387,8 +412,6 @@ bool PassRunner::step(std::vector<Instr> &out)
     std::vector<int64_t> counts;
     int64_t base = 0;
     for (int step = 0; step < r_; ++step) {
-        std::fill(targets.begin(), targets.end(), 0);
-        ps.closure(cur.data(), &targets);
         int64_t best_a = base;
         bool found = false;
         // with no qubit moved out a placement reaches at least as many gates
@@ -428,7 +451,7 @@ bool PassRunner::step(std::vector<Instr> &out)
         double best_rate = 0.0;
         for (int b = (int)prefix.size(); b >= 1; --b) {
             int64_t cls[3] = {0, 0, 0};
-            const int64_t a = ps.closure(prefix[b - 1].data(), nullptr, cls);
+            const int64_t a = ps.closure(prefix[b - 1].data(), cls);
             int changed = 0;
             for (int q = 0; q < n; ++q)
                 changed += prefix[b - 1][q] != sigma_[q];
@@ -891,14 +914,14 @@ int schedule_segment(const std::vector<LGate> &lg, const qs_gate *g, const std::
     const Dag dag = build_dag(g, gi, nq, &from);
     std::vector<int> npend(cnt), ready;
     for (int v = 0; v < cnt; ++v) {
-        npend[v] = (int)dag.pred[v].size();
+        npend[v] = dag.n_pred(v);
         if (npend[v] == 0)
             ready.push_back(v);
     }
     std::vector<char> emitted(cnt, 0);
     auto emit = [&](int v, auto &&now_ready) {
         emitted[v] = 1;
-        for (int s : dag.succ[v])
+        for (int s : dag.succs(v))
             if (--npend[s] == 0)
                 now_ready(s);
     };
@@ -1093,7 +1116,7 @@ int schedule_segment(const std::vector<LGate> &lg, const qs_gate *g, const std::
                     if (needs_reg(v) && !((bits >> lg[v].tb) & 1u))
                         continue;
                     ++run;
-                    for (int s : dag.succ[v]) {
+                    for (int s : dag.succs(v)) {
                         if (seen[s] != stamp) {
                             seen[s] = stamp;
                             sim[s] = npend[s];

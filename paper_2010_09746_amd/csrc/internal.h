@@ -164,8 +164,18 @@ std::vector<Instr> run_pass(const qs_gate *g, int64_t ng, int n, int m, int r, i
                             const std::vector<int> &sigma0, PassStats *st);
 
 class PassState;
+// Dependency graph: the predecessors of node v (ascending) are pred[pred_at[v]]
+// .. pred[pred_at[v + 1] - 1], its successors the same of succ.
 struct Dag {
-    std::vector<std::vector<int>> pred, succ;
+    std::vector<size_t> pred_at, succ_at;
+    std::vector<int> pred, succ;
+    struct Range {
+        const int *first, *last;
+        const int *begin() const { return first; }
+        const int *end() const { return last; }
+    };
+    int n_pred(int v) const { return (int)(pred_at[v + 1] - pred_at[v]); }
+    Range succs(int v) const { return {succ.data() + succ_at[v], succ.data() + succ_at[v + 1]}; }
 };
 // The same pass, one iteration per step(): the instructions of the sweep and
 // the PermuteQubits (or global gate) that follows it are appended to out;
