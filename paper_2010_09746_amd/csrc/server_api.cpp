@@ -377,6 +377,7 @@ qs_status qs_server_admit(qs_server *s, const qs_program *pp, void *state_buf, s
                 P.t.ops = d_ops;
             }
             P.t.n_hi = n - s->K;
+            P.t.io |= IO_TOUCH;  // in the shared launch
             P.ntiles = (uint32_t)ntiles;
             P.last = 0;
             P.zpos = 0;
@@ -479,10 +480,12 @@ qs_status qs_server_step_launch(qs_server *s, int *n_running)
             for (size_t i = 0; i < solo.size(); ++i) {
                 const BatchPass *P = solo[i];
                 hipStream_t st = s->side[i % ns];
+                TileArgs t = P->t;
+                t.io = (t.io & ~IO_TOUCH) | touch_flag(P->ntiles, s->log_nt);
                 if (s->dt == QS_C64)
-                    launch_tile_f32(P->t, P->ntiles, s->log_r, s->log_nt, st);
+                    launch_tile_f32(t, P->ntiles, s->log_r, s->log_nt, st);
                 else
-                    launch_tile_f64(P->t, P->ntiles, s->log_r, s->log_nt, st);
+                    launch_tile_f64(t, P->ntiles, s->log_r, s->log_nt, st);
             }
             for (int i = 0; i < ns; ++i) {
                 hipchk(hipEventRecord(s->join_ev[i], s->side[i]), "hipEventRecord");

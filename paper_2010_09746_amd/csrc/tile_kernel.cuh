@@ -572,9 +572,8 @@ template <typename R, int LOG_NT, int LOG_R, bool STREAM = true> struct TileKern
     // reach one otherwise waits for a miss to memory at each of them (the caches start
     // a launch without them): with one or two workgroups per compute unit
     // nothing hides that.  The wavefronts of the workgroup split the lines,
-    // 16 in flight each.  21 qubits, complex64, 30 layers: 39 -> 32 us per
-    // pass (512 workgroups); 26 qubits and above unchanged.  (Vector loads
-    // instead, which stop at the second-level cache: 33 us.)
+    // 16 in flight each.  (Vector loads instead, which stop at the
+    // second-level cache, gain less.)  Not in every pass: touch_flag.
     static __device__ __forceinline__ void touch_records(OpPtr ops, int n_ops, uint32_t tid)
     {
         using WP = const __attribute__((address_space(4))) uint32_t *;
@@ -739,7 +738,7 @@ template <typename R, int LOG_NT, int LOG_R, bool STREAM = true> struct TileKern
         };
         for (uint64_t t = t_first; t < t_end; t += t_step) {
             load(v, t);
-            if (t == t_first)
+            if (t == t_first && (a.io & IO_TOUCH))
                 touch_records(ops, n_ops, tid);
             // wait for the tile here (vmcnt(0); expcnt and lgkmcnt left at their
             // maxima), so that the operations wait for no global access

@@ -21,6 +21,9 @@ std::map<void *, size_t> blocks;
 hipError_t malloc_error = hipSuccess;  // returned by every hipMalloc when set
 int device = 0;
 int queue_grid = 0;
+uint64_t tile_launches[2] = {};  // those that read their records ahead, the others
+
+void tile_launch(const TileArgs &a) { ++tile_launches[(a.io & IO_TOUCH) ? 0 : 1]; }
 
 [[noreturn]] void not_here(const char *what) { fail(QS_ERR_UNSUPPORTED, std::string("no host version of ") + what); }
 
@@ -34,6 +37,12 @@ size_t host_used() { return used; }
 long host_mallocs() { return mallocs; }
 void host_set_malloc_error(int e) { malloc_error = (hipError_t)e; }
 void host_set_device(int d) { device = d; }
+void host_tile_launches(uint64_t *ahead, uint64_t *others)
+{
+    *ahead = tile_launches[0];
+    *others = tile_launches[1];
+    tile_launches[0] = tile_launches[1] = 0;
+}
 int host_queue_grid() { return queue_grid; }  // workgroups of the last batch launch
 
 // ---- HIP
@@ -137,8 +146,8 @@ size_t fid_work_doubles(int) { return 5; }
 
 void launch_plain_gate(void *, qs_dtype, int, const qs_gate &, hipStream_t) { not_here("a plain gate"); }
 void launch_involution(void *, qs_dtype, int, const std::vector<int> &, hipStream_t) {}
-void launch_tile_f32(const TileArgs &, uint64_t, int, int, hipStream_t) {}
-void launch_tile_f64(const TileArgs &, uint64_t, int, int, hipStream_t) {}
+void launch_tile_f32(const TileArgs &a, uint64_t, int, int, hipStream_t) { tile_launch(a); }
+void launch_tile_f64(const TileArgs &a, uint64_t, int, int, hipStream_t) { tile_launch(a); }
 void launch_tile_f32_z(const TileArgs &, uint64_t, int, int, double *, hipStream_t) { not_here("a tile pass"); }
 void launch_tile_f64_z(const TileArgs &, uint64_t, int, int, double *, hipStream_t) { not_here("a tile pass"); }
 void launch_batch_init(void *, qs_dtype, uint64_t, const uint64_t *, int, hipStream_t) { not_here("a batch"); }
