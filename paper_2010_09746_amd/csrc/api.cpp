@@ -398,7 +398,10 @@ void launch_range(qs_state *s, const Program &p, size_t a_idx, size_t b_idx, con
             a.ops = d_ops + L.op_begin;
             a.n_hi = s->n - L.k;
             const uint64_t tiles = 1ull << (s->n - L.k);
-            a.io |= touch_flag(tiles, L.log_nt) | (basis ? IO_BASIS : 0u);
+            if (!reads_ahead(a.io, tiles, L.log_nt))
+                a.n_touch = 0;
+            if (basis)
+                a.io |= IO_BASIS;
             // a pass from the basis state reads nothing
             timed(s->stream, P_TILE, (basis ? 1.0 : 2.0) * (double)s->bytes, [&] {
                 if (zparts && s->dt == QS_C64)

@@ -396,7 +396,6 @@ qs_status qs_batch_create(int count, const int *n_qubits, const qs_gate *const *
                 D.t.n_hi = b->n[c] - P.k;
                 if (P.level == 0)
                     D.t.io |= IO_BASIS;  // the first pass starts from |0...0> instead of reading the state
-                D.t.io |= IO_TOUCH;
                 D.ntiles = P.tiles;
                 D.last = P.last;
                 D.zpos = bp.progs[c].sigma_final[0];

@@ -1673,7 +1673,7 @@ void set_direct_io(Launch &L, const std::vector<TileOp> &ops, qs_dtype dt)
 
 void tile_args_from_launch(const Launch &L, TileArgs &a)
 {
-    a.n_ops = L.op_count;
+    a.n_ops = a.n_touch = L.op_count;
     for (int b = 0; b < 16; ++b)
         a.pos[b] = (uint8_t)(b < L.k ? L.pos[b] : 0);
     a.io = L.io;

@@ -377,7 +377,6 @@ qs_status qs_server_admit(qs_server *s, const qs_program *pp, void *state_buf, s
                 P.t.ops = d_ops;
             }
             P.t.n_hi = n - s->K;
-            P.t.io |= IO_TOUCH;  // in the shared launch
             P.ntiles = (uint32_t)ntiles;
             P.last = 0;
             P.zpos = 0;
@@ -481,7 +480,8 @@ qs_status qs_server_step_launch(qs_server *s, int *n_running)
                 const BatchPass *P = solo[i];
                 hipStream_t st = s->side[i % ns];
                 TileArgs t = P->t;
-                t.io = (t.io & ~IO_TOUCH) | touch_flag(P->ntiles, s->log_nt);
+                if (!reads_ahead(t.io, P->ntiles, s->log_nt))
+                    t.n_touch = 0;
                 if (s->dt == QS_C64)
                     launch_tile_f32(t, P->ntiles, s->log_r, s->log_nt, st);
                 else

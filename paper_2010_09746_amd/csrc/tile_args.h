@@ -60,18 +60,23 @@ constexpr uint32_t REMAP_CNOTS = 2u;
 constexpr int REMAP_COUNT = 8, REMAP_IMG = 5, REMAP_LANE = 10, REMAP_LANES = 4;
 constexpr uint32_t IO_BASIS = 16u;
 constexpr uint32_t IO_EXT = 32u;
-constexpr uint32_t IO_TOUCH = 64u;
-// IO_TOUCH of a pass run as one launch of `tiles` workgroups of 2^log_nt
-// threads: at up to 2^10 of them its records are read ahead
-// (TileKernel::touch_records).  With more, other workgroups hide the misses,
-// and one or two wavefronts would read the whole table for a single tile; four
-// or more share it.  Programs with against without, by tiles per pass: one
-// wavefront, 64 to 1024 tiles 0.90-0.93 of the time, 2048 0.98-1.05, 4096
-// 1.05, 16384 of 2^8 amplitudes (22 qubits, 20 layers, complex64) 1257 against
-// 938 us, 32768 of 2^9 2655 against 2254; two, 4096 tiles 1.01; four, 256 tiles
-// 0.93, 1024 1.00, 4096 of 2^12 (24 qubits, random family) 1529 against 1558 us
-// complex128, 1002 against 991 complex64, 16384 and more 0.99-1.00.
-inline uint32_t touch_flag(uint64_t tiles, int log_nt) { return tiles <= 1024 || log_nt >= 8 ? IO_TOUCH : 0u; }
+// Whether the workgroups of a pass run as one launch of `tiles` tiles of
+// 2^log_nt threads read its records ahead (TileArgs::n_touch).  At up to 2^10
+// tiles they do.  With more, other workgroups hide the misses, and one or two
+// wavefronts would read the whole table for a single tile; four or more share
+// it.  Programs with against without, by tiles per pass: one wavefront, 64 to
+// 1024 tiles 0.90-0.93 of the time, 2048 0.98-1.05, 4096 1.05, 16384 of 2^8
+// amplitudes (22 qubits, 20 layers, complex64) 1257 against 938 us, 32768 of
+// 2^9 2655 against 2254; two, 4096 tiles 1.01; four, 256 tiles 0.93, 1024
+// 1.00, 4096 of 2^12 (24 qubits, random family) 1529 against 1558 us
+// complex128, 1002 against 991 complex64, 16384 and more 0.99-1.00.  Passes
+// over partial lines (no streaming access) always do: 0.77-0.98 at any number
+// of tiles of any size (22 qubits, tiles of 2^10, 12 layers, complex128: 873
+// against 1005 us, complex64 677 against 735).
+inline bool reads_ahead(uint32_t io, uint64_t tiles, int log_nt)
+{
+    return !(io & 8u) || tiles <= 1024 || log_nt >= 8;
+}
 
 // One operation of a fused tile pass (104 bytes, every field at least 32 bits
 // wide and naturally aligned so that the kernel reads it with scalar loads).  Its controls are split by
@@ -134,10 +139,9 @@ struct TileArgs {
                                   // bit 4 (IO_BASIS): nothing is read, the tiles start as
                                   // the basis state |0...0> (1 at physical index 0);
                                   // bit 5 (IO_EXT): the pass holds OP_LANE or OP_FAN records or
-                                  // permutes its store (bit 2);
-                                  // bit 6 (IO_TOUCH): read the records ahead while a
-                                  // workgroup's first tile loads
-    int32_t pad;
+                                  // permutes its store (bit 2)
+    int32_t n_touch;              // records to read ahead while a workgroup's first tile loads:
+                                  // n_ops, or 0 for none (reads_ahead)
     uint8_t sperm[16];            // tile bit b moves to tile bit sperm[b] (io bit 2)
 };
 static_assert(sizeof(TileArgs) == 112, "TileArgs layout");

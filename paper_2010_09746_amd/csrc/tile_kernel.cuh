@@ -573,11 +573,11 @@ template <typename R, int LOG_NT, int LOG_R, bool STREAM = true> struct TileKern
     // a launch without them): with one or two workgroups per compute unit
     // nothing hides that.  The wavefronts of the workgroup split the lines,
     // 16 in flight each.  (Vector loads instead, which stop at the
-    // second-level cache, gain less.)  Not in every pass: touch_flag.
-    static __device__ __forceinline__ void touch_records(OpPtr ops, int n_ops, uint32_t tid)
+    // second-level cache, gain less.)  Not in every pass: reads_ahead.
+    static __device__ __forceinline__ void touch_records(OpPtr ops, int n_touch, uint32_t tid)
     {
         using WP = const __attribute__((address_space(4))) uint32_t *;
-        const uint32_t lines = ((uint32_t)n_ops * (uint32_t)sizeof(TileOp)) >> 6;  // whole lines: reads stay inside
+        const uint32_t lines = ((uint32_t)n_touch * (uint32_t)sizeof(TileOp)) >> 6;  // whole lines: reads stay inside
         const WP p = (WP)ops;
         constexpr uint32_t U = 16, NW = NT / 64;
         const uint32_t wave = NW > 1 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6)) : 0u;
@@ -738,8 +738,8 @@ template <typename R, int LOG_NT, int LOG_R, bool STREAM = true> struct TileKern
         };
         for (uint64_t t = t_first; t < t_end; t += t_step) {
             load(v, t);
-            if (t == t_first && (a.io & IO_TOUCH))
-                touch_records(ops, n_ops, tid);
+            if (t == t_first)
+                touch_records(ops, a.n_touch, tid);
             // wait for the tile here (vmcnt(0); expcnt and lgkmcnt left at their
             // maxima), so that the operations wait for no global access
             __builtin_amdgcn_s_waitcnt(0x0F70);

@@ -23,7 +23,7 @@ int device = 0;
 int queue_grid = 0;
 uint64_t tile_launches[2] = {};  // those that read their records ahead, the others
 
-void tile_launch(const TileArgs &a) { ++tile_launches[(a.io & IO_TOUCH) ? 0 : 1]; }
+void tile_launch(const TileArgs &a) { ++tile_launches[a.n_touch ? 0 : 1]; }
 
 [[noreturn]] void not_here(const char *what) { fail(QS_ERR_UNSUPPORTED, std::string("no host version of ") + what); }
 

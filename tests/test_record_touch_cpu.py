@@ -28,7 +28,8 @@ def test_states_run_by_themselves(n, k, ahead, dt):
         buf = np.zeros((2 << n) + 4, dtype=np.float32 if dt == "c64" else np.float64)
         buf = buf[(-buf.ctypes.data % 16) // buf.itemsize:][: 2 << n]
         st = Q.qs_state_create(n, dt, buf.ctypes.data, buf.nbytes, 0)
-        o = Q.make_opts(k_tile=k, max_swaps=8, pinned=2, perm_exec="relabel")
+        # whole 128-byte lines
+        o = Q.make_opts(k_tile=k, max_swaps=8, pinned=4 if dt == "c64" else 3, perm_exec="relabel")
         for g in (layered_circuit(n, 4, n), paper_random_circuit(n, 6 * n, 0.5, n)):
             p = Q.qs_compile(g, n, dt, None, o)
             passes = Q.qs_program_get_stats(p)["n_tile_passes"]
@@ -38,4 +39,22 @@ def test_states_run_by_themselves(n, k, ahead, dt):
             Q.qs_run_circuit(st, g, o)
             assert _launches(L) == ((passes, 0) if ahead else (0, passes))
             Q.qs_program_destroy(p)
+        Q.qs_state_destroy(st)
+
+
+@pytest.mark.parametrize("n,k", [(12, 9), (21, 7), (21, 9)])
+def test_passes_over_partial_lines_always_do(n, k):
+    with host_library() as L:
+        buf = np.zeros((2 << n) + 4, dtype=np.float32)
+        buf = buf[(-buf.ctypes.data % 16) // 4:][: 2 << n]
+        st = Q.qs_state_create(n, "c64", buf.ctypes.data, buf.nbytes, 0)
+        # every qubit below the line leaves it by an exchange: no pass moves whole lines but the first
+        o = Q.make_opts(k_tile=k, max_swaps=16, pinned=0, perm_exec="relabel")
+        p = Q.qs_compile(layered_circuit(n, 6, n), n, "c64", None, o)
+        passes = Q.qs_program_get_stats(p)["n_tile_passes"]
+        _launches(L)
+        Q.qs_run_program(st, p)
+        ahead, others = _launches(L)
+        assert ahead + others == passes and ahead >= passes - 2
+        Q.qs_program_destroy(p)
         Q.qs_state_destroy(st)
