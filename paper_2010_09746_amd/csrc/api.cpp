@@ -1161,10 +1161,11 @@ qs_status qs_read_state(qs_state *s, double *out)
         // (16 MiB of the state's read-out workspace) at a time, fewer where
         // the device has less room.  Without room for 2^10, or with another
         // device than the state's current, the host does it, as the copy
-        // alone needs neither.
+        // alone needs neither; also up to 7 qubits, where its loop is shorter
+        // than a launch (21.6 against 23.3 us a call, 23.0 against 23.3 at 8).
         int cur = -1;
         hipchk(hipGetDevice(&cur), "hipGetDevice");
-        uint64_t chunk = cur == s->dev ? std::min<uint64_t>(N, 1ull << 20) : 0;
+        uint64_t chunk = cur == s->dev && s->n > 7 ? std::min<uint64_t>(N, 1ull << 20) : 0;
         while (chunk)
             try {
                 ensure_work(s, 2 * chunk);
