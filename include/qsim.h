@@ -448,7 +448,8 @@ typedef struct {
  * that completes a circuit's last pass reduces its read-out.  The library
  * allocates one device buffer holding every state (complex64 or complex128),
  * the compiled tables and its own HIP stream.  Compilation runs on host
- * threads. */
+ * threads.  Controlled phases that share a qubit run one operation each here, not
+ * in groups as in qs_run_program. */
 qs_status qs_batch_create(int count, const int *n_qubits, const qs_gate *const *gates, const int64_t *n_gates,
                           qs_dtype dt, const qs_batch_opts *opts, qs_batch **out);
 /* Enqueue one run: a small kernel that clears the run's counters, then the

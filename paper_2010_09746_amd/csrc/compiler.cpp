@@ -513,11 +513,16 @@ int small_state_reg_bits(int n, int k, qs_dtype dt)
     // amplitudes per thread, and the time of a wavefront's own chain of
     // instructions is what counts: more, shorter wavefronts are faster although
     // they re-lay registers out more often.  Measured at 20 layers, k = 12, 16
-    // against 8 amplitudes per thread: complex64 14 qubits 189, 159 us, 18: 263,
-    // 224, 21: 354, 342, 22: 486, 535; complex128 14 qubits 181, 158, 18: 257, 226,
+    // against 8 amplitudes per thread: complex64 14 qubits 192, 166 us, 18: 260,
+    // 228, 21: 354, 342, 22: 486, 535; complex128 14 qubits 179, 152, 18: 261, 231,
     // 21: 406, 377, 22: 620, 666 (the same line at k = 9, 10, 11).  A
     // complex64 state that is one tile runs alone on its compute unit: 4
-    // amplitudes per thread (10 qubits 129, 107, 94 us with 16, 8, 4).
+    // amplitudes per thread.  By amplitudes per thread 16, 8, 4, 2 (the clamp to
+    // 64 and 1024 threads leaves fewer shapes at 7, 8 and from 13 qubits on):
+    // complex64 9 qubits 92, 92, 81, 94 us, 10: 129, 105, 98, 112, 11: 135, 116,
+    // 104, 138, 12: 168, 135, 130 (2^10 threads, the most); 7, 8 and 13: the same
+    // within 1% whichever is asked for.  complex128 keeps 8: 9 qubits 78, 79, 91,
+    // 85 us, 10: 112, 91, 115, 100, 11: 120, 105, 122, 129, 12: 157, 122.
     if (n > 21)
         return pass_reg_bits(k, dt);
     return dt == QS_C64 && n == k ? 2 : 3;
@@ -1308,10 +1313,12 @@ void fuse_phase_fans(std::vector<TileOp> &ops, size_t begin)
 // REMAP_IMG + s), M of a thread's part differs from it by a constant for each
 // thread bit that is a control (words REMAP_LANE + e), at most REMAP_LANES of
 // them; the wavefront bits keep their tile bits.  55% of the exchanges of the
-// CNOT-only random family go this way (26 qubits), 20% at one CNOT in three,
-// few in layered circuits (a one-qubit gate follows each CNOT in the same
-// layout).  20 qubits complex64, CNOTs only: 390 -> 312 us; 26 qubits, 70% CNOTs:
-// 7.91 -> 7.51 ms; 30%: 6.34 -> 6.20 ms.
+// CNOT-only random family go this way, 20% at one CNOT in three, few in
+// layered circuits (a one-qubit gate follows each CNOT in the same layout).
+// Random family by its share of CNOTs, without and with: 20 qubits complex64 30%
+// 278, 269 us, 70% 352, 314, CNOTs only 385, 305; complex128 321, 312; 401, 357;
+// 457, 365; 26 qubits complex64 6.18, 6.06 ms; 7.30, 6.90; 8.26, 8.13; complex128
+// 10.29, 10.09; 12.68, 12.47; 15.99, 15.87.
 void absorb_exchanges(std::vector<TileOp> &ops, size_t begin, int k, int log_r)
 {
     std::vector<size_t> rl;

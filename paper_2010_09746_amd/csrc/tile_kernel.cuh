@@ -604,10 +604,9 @@ template <typename R, int LOG_NT, int LOG_R, bool STREAM = true> struct TileKern
     // thread bits and outside the tile multiply into one factor per lane, which
     // the amplitudes whose hub bit is 1 then take in one multiplication;
     // the spokes on register slots follow one by one.  A Fourier transform's
-    // 26 controlled phases on one target cost about 250 vector instructions
-    // per wavefront this way instead of 26 multiplications of up to 16
-    // amplitudes each: the
-    // transform of 27 qubits, complex128: 17.3 -> 7.0 ms.
+    // 26 controlled phases on one target cost about 250 vector instructions per
+    // wavefront this way instead of 26 multiplications of up to 16 amplitudes
+    // each: the transform of 27 qubits, complex128: 17.3 -> 7.0 ms.
     static __device__ __forceinline__ void fan(int nc, OpPtr ops, int oi, C (&v)[NR], uint32_t fl, uint32_t tbase,
                                                uint64_t base)
     {
@@ -701,10 +700,12 @@ template <typename R, int LOG_NT, int LOG_R, bool STREAM = true> struct TileKern
         // made only before the stores, from a copy of the thread id that the
         // compiler does not know, so that it occupies no registers while the
         // operations run: 80 instead of 88 vector registers, six wavefronts per
-        // SIMD instead of five (29 qubits, 50 layers: 139.3 -> 137.1 ms; 26
-        // qubits, random family: 6.30 -> 6.16 ms).  With fewer amplitudes it
-        // is better off the end of a short chain (21 qubits: 565 against 573
-        // us), and complex128 gains no wavefront.
+        // SIMD instead of five (20 layers: 28 qubits 27.6 -> 27.1 ms, 24 qubits
+        // 1655 -> 1635 us; the random family at 26 and 28 qubits within 1%).  At
+        // 22 qubits, where every wavefront of a pass is in flight at once, the
+        // longer chain costs 2% (487 -> 497 us).  With fewer amplitudes it is
+        // better off the end of a short chain (21 qubits: 565 against 573 us),
+        // and complex128 gains no wavefront.
         constexpr bool LATE_ST = sizeof(R) == 4 && LOG_R == 4;
         uint64_t lane_st = LATE_ST ? 0 : lane_offset(a.st_lane, tid);
         auto pbit_ld = [&](int s) { return 1ull << a.ld_reg[s]; };
