@@ -60,3 +60,11 @@ def test_another_current_device():
         assert np.array_equal(Q.qs_read_state(h, 10), want)
         assert L.host_used() == 0
         L.host_set_device(0)
+
+
+@pytest.mark.parametrize("dt", ["c64", "c128"])
+@pytest.mark.parametrize("n,launches", [(1, False), (7, False), (8, True), (13, True)])
+def test_few_amplitudes_are_ordered_by_the_host(n, launches, dt):
+    with host_library() as L, _state(n, dt, n) as (h, want):
+        assert np.array_equal(Q.qs_read_state(h, n), want)
+        assert (L.host_used() > 0) == launches  # the workspace that the device's part of the work needs
