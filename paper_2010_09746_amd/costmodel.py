@@ -84,12 +84,12 @@ def calibration_circuits(n: int, k: int, log_r: int, seed: int = 20100946 + 9) -
         "neg": [U(0)] + [(KIND_CZ, q % (k - 1), q % (k - 1) + 1, None) for q in range(N)],
         "diag": [U(0)] + [(KIND_U, q % R, -1, phase(0.1 + 0.01 * q)) for q in range(N)],
         "dispatch": [U(0)] + [(KIND_CX, n - 1, q % R, None) for q in range(N)],
-        # a dependency chain over all tile qubits: each gate's target is the
-        # previous gate's, so most steps need a new register layout
         # controlled phases around two qubits in turn, with three or all of the
         # tile's qubits beyond the register slots at a time
-        "fan": [U(q) for q in range(R)] + fans(3),
-        "fan_phase": [U(q) for q in range(R)] + fans(len(rim)),
+        "fan": [U(q) for q in range(R)] + fans(3) if rim else None,
+        "fan_phase": [U(q) for q in range(R)] + fans(len(rim)) if rim else None,
+        # a dependency chain over all tile qubits: each gate's target is the
+        # previous gate's, so most steps need a new register layout
         "remap": [g for i in range(N // 2) for g in (U((st * i) % k), (KIND_CX, (st * i) % k, (st * i + st) % k, None))],
     }
     return {name: make_gates(g) for name, g in c.items() if g is not None}
@@ -192,6 +192,8 @@ class CostModel:
         shape = self._shape(n, k, reg_bits)
         self.calibrate([shape])
         tc = self.tile_costs[shape]
+        # costs measured without the phases that run in groups price each as a diagonal gate
+        tc = {"fan": 0.0, "fan_phase": tc["diag"], **tc}
         ms = sum(w * tc[c] for c, w in zip(TILE_CLASSES, tile_work(counts)))
         # a pending phase applied on its own touches half the amplitudes of
         # a diagonal update (rare: the W that left it ended an earlier pass)

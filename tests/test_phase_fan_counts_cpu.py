@@ -49,6 +49,23 @@ def test_predictions_do_not_price_grouped_phases_as_diagonal_gates():
     assert ms == c["diag"] - c["fan_phase"] < 0.5 * c["diag"]
 
 
+def test_costs_without_the_classes_of_groups_price_phases_one_by_one():
+    cm = costmodel.CostModel("c128", n_cal=24)
+    cm.launch_costs = {c: 0.0 for c in ("plain_u", "plain_cu", "plain_cx", "plain_cz", "move", "move_fraction")}
+    cm.tile_costs = {(12, 0): {c: 2.0 if c == "diag" else 0.0 for c in costmodel.TILE_CLASSES if "fan" not in c}}
+    ms, c = cm.predict(qft_circuit(24), 24, k_tile=12, max_swaps=4, pinned=3, perm_exec="relabel")
+    assert ms == 2.0 * c["diag"] and c["fan_phase"] > 0
+
+
+@pytest.mark.parametrize("k", range(2, 15))
+def test_calibration_circuits_of_every_tile(k):
+    for log_r in range(1, 6):
+        for dt in ("c64", "c128"):
+            for name, g in costmodel.calibration_circuits(20, k, log_r).items():
+                Q.Program(g, 20, dt, form="pass", k_tile=k, max_swaps=1, pinned=min(k, 3) - 1, perm_exec="relabel",
+                          reg_bits=log_r).close()
+
+
 @pytest.mark.parametrize("k,log_r", [(7, 1), (9, 3), (12, 4), (13, 5)])
 def test_calibration_separates_groups_from_their_phases(k, log_r):
     rows = [costmodel.tile_work(_counts(g, 22, k, reg_bits=log_r, max_swaps=1, **costmodel.CAL_OPTS.get(name, {})))
