@@ -173,7 +173,13 @@ class CostModel:
     def _shape(self, n: int, k: int, reg_bits: int) -> tuple:
         """Key of the tile costs that programs of n qubits with these options have."""
         log_r = self._log_r(k, reg_bits, n)
-        return (k, reg_bits) if log_r == self._log_r(k, reg_bits) else (k, log_r)
+        if log_r == self._log_r(k, reg_bits):
+            return k, reg_bits
+        # costs brought along to a host that cannot measure the shape's own:
+        # those of the same options
+        if (k, log_r) not in self.tile_costs and (k, reg_bits) in self.tile_costs and not torch.cuda.is_available():
+            return k, reg_bits
+        return k, log_r
 
     def calibrate(self, shapes) -> None:
         shapes = [s for s in shapes if s not in self.tile_costs]

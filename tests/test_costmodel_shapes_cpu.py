@@ -62,3 +62,12 @@ def test_calibration_is_of_the_shape_it_names(monkeypatch):
     cm.calibrate_tile(None, 12, 4)
     assert by_default == seen
     assert set(cm.tile_costs) == {(12, 0), (12, 4)}
+
+
+def test_costs_brought_to_a_host_without_a_device(monkeypatch):
+    """Nothing can measure the small state's shape there: the costs given for the options still price it."""
+    monkeypatch.setattr(costmodel.torch.cuda, "is_available", lambda: False)
+    cm = _model("c128", tile_costs={(12, 0): 1.0})
+    ms, counts = cm.predict(layered_circuit(16, 6, 16), 16, **OPTS)
+    assert ms > 0 and set(cm.tile_costs) == {(12, 0)}
+    assert cm.choose(layered_circuit(16, 6, 16), 16, ks=(12,), rs=(8,))[1][0]["predicted_ms"] == ms
