@@ -62,8 +62,9 @@ class Server:
     def compile(self, gates, n) -> Q.Program:
         # the server's tile shape by name: a small state compiled for a run of its
         # own gets another one, and admission would compile it again
+        reg_bits = Q.qs_tile_reg_bits(0, self.dtype, self.k_tile, self.reg_bits)
         return Q.Program(gates, n, self.dtype, form="pass", k_tile=self.k_tile, max_swaps=self.max_swaps,
-                         pinned=self.pinned, perm_exec="relabel", reg_bits=Q.qs_tile_reg_bits(0, self.dtype, self.k_tile, self.reg_bits))
+                         pinned=self.pinned, perm_exec="relabel", reg_bits=reg_bits)
 
     def serve(self, requests, realtime=True, log=None):
         """requests: dicts with id, arrival (s), n, gates, samples.  Returns
